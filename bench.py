@@ -62,12 +62,17 @@ HBM_PEAK_GBS = 8000.0
 # valid only for the schedule and kernel version recorded, null otherwise.
 HEADLINE_TRAFFIC = {"schedule": {"tile": 3, "sk_tiles": 64, "sk_blocks": 512, "even": 1}, "kernel_version": "k11",
                     "bytes": 971436304}
-KERNEL_VERSION = "k11"
+KERNEL_VERSION = "k12"
 
 
 def headline_kernels(d):
     # the headline's output is whole 128 x 128 tiles over whole K steps: tile
     # 3 runs its unmasked variant (last template argument true)
+    if d.get("packed"):
+        # the packed gather kernel: C is written in whole 64-byte segments, so streamed
+        p = d["packed"] - 1
+        return ["packed_kernel<double, %d, 0, 1, true>" % p] + (
+            ["packed_fixup_kernel<double, %d, true>" % p] if d["packed_shares"] else [])
     t = d["tile"]
     full = ", true" if t == 3 else ""
     if d.get("sk_tiles") and d.get("even"):

@@ -139,7 +139,12 @@ typedef enum {
  *         the matrix through a matrix-vector kernel instead, its summation
  *         cut into slabs whose partial sums are added in a fixed order
  *         (environment variable COMET_GEMV=0 keeps the tiles;
- *         COMET_GEMV_SPLIT=n asks for about n slabs).
+ *         COMET_GEMV_SPLIT=n asks for about n slabs).  Other native products
+ *         run in the packed kernel, which loads single elements and so takes
+ *         any strides and extents, unless an operand reaches 2 GiB, the
+ *         summation is short and the output large, or a gather tile or
+ *         schedule is forced (COMET_PACKED=0 keeps the vector-load tiles;
+ *         COMET_PACKED=tile,whole,shares forces its schedule).
  *   TTGT  transpose-transpose-GEMM-transpose (Section 2; Section 6 "TTGT"):
  *         A and B are permuted into matrices, multiplied, and the product is
  *         permuted into C.  The flattening (Section 6 "Optimal permutation
@@ -245,7 +250,10 @@ comet_status_t comet_plan_execute_noalloc(comet_plan_t plan, double alpha, const
  * pieces), persistent workgroups, resident workgroups per CU, the
  * short-summation kernel's workgroups (shortk), the matrix-vector kernel
  * (gemv: 1 reads the matrix along the output, 2 along the summation; 0 not
- * used) and its summation slabs (gemv_split), the split tile and whether
+ * used) and its summation slabs (gemv_split), the packed gather kernel
+ * (packed > 0: it runs instead of the tile kernels above, with its tile
+ * packed - 1; packed_whole output tiles are computed whole and the steps of
+ * the others shared by packed_shares workgroups), the split tile and whether
  * FP32 BF16x3 runs fused, TTGT permutations with their Section 6 cost and
  * modelled time (model_us).  COMET_ERR_WORKSPACE if buf is too small (the
  * text is truncated). */

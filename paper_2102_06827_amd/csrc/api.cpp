@@ -81,6 +81,7 @@ struct comet_plan_s {
   void *dtables = nullptr;     // the six offset tables (and three batch tables), one device allocation
   GettTables t{};
   const int64_t *offAx = nullptr, *offBx = nullptr, *offCx = nullptr;   // batch tables (device), or null
+  PackedLaunch pk{};           // the packed gather kernel's tables and sizes (am null: it cannot run this problem)
   bool vecA_tables = false, vecB_tables = false;
   bool fused3 = false;         // FP32 operands split into BF16x3 inside the gather kernel
   size_t ws_bytes = 0;
@@ -91,6 +92,7 @@ struct comet_plan_s {
   PermuteLaunch permA{}, permB{}, permC{};
   size_t wsA = 0, wsB = 0, wsC = 0;   // byte offsets of A_p, B_p, C_p in the workspace
   size_t wsG = 0;                     // byte offset of the GEMM stage's own workspace
+  size_t ws_taken = 0;                // TTGT's GEMM stage: bytes of the copies ahead of its own workspace
   size_t sk_bytes = 0;                // stream-K partial sums (at offset 0 of a GETT plan's workspace)
 
   ~comet_plan_s() {
@@ -132,6 +134,31 @@ struct comet_batch_s {
 
 namespace {
 
+// Whether the packed gather kernel can run the contraction: arithmetic in
+// the storage type, offsets that fit its 32-bit byte tables, sizes that fit
+// an int (with a tile's overhang).
+bool packed_can(const Analysis &an) {
+  const bool native = an.dtype == COMET_F64 ? an.compute == COMET_COMPUTE_F64 : an.compute == COMET_COMPUTE_F32;
+  const int64_t lim = kPackedMaxBytes / int64_t(elem_size(an.dtype));
+  const int64_t sizes = int64_t(INT32_MAX) - 1024;
+  return native && !an.empty_out && !an.empty_sum && an.sizeA < lim && an.sizeB < lim &&
+         an.m < sizes && an.n < sizes && an.k < sizes;
+}
+
+// Whether C's offsets come in whole 64-byte segments along n, aligned to 64
+// bytes from C's base.
+bool c_segments(const Analysis &an) {
+  const int64_t w = 64 / int64_t(elem_size(an.dtype));
+  if (an.n % w) return false;
+  for (int64_t m : an.offCm)
+    if (m % w) return false;
+  for (size_t j = 0; j < an.offCn.size(); ++j)
+    if (j % w ? an.offCn[j] != an.offCn[j - 1] + 1 : an.offCn[j] % w != 0) return false;
+  for (int64_t x : an.offCx)
+    if (x % w) return false;
+  return true;
+}
+
 comet_status_t upload_tables(comet_plan_s *p) {
   const Analysis &an = p->an;
   const std::vector<int64_t> *tabs[9] = {&an.offAm, &an.offAk, &an.offBk, &an.offBn, &an.offCm,
@@ -141,10 +168,28 @@ comet_status_t upload_tables(comet_plan_s *p) {
     off[i] = total;
     total += align256(std::max<size_t>(tabs[i]->size(), 1) * sizeof(int64_t));
   }
+  // the packed kernel's tables: byte offsets in 32 bits, the last entry
+  // repeated over the padding
+  const bool packed = packed_can(an);
+  const size_t es = elem_size(an.dtype);
+  size_t poff[4] = {0, 0, 0, 0}, plen[4] = {0, 0, 0, 0};
+  for (int i = 0; packed && i < 4; ++i) {
+    const size_t n = tabs[i]->size();
+    plen[i] = i == 0 || i == 3 ? (n + kPackedRowPad - 1) / kPackedRowPad * kPackedRowPad : n + kPackedKPad;
+    poff[i] = total;
+    total += align256(plen[i] * sizeof(uint32_t));
+  }
   HIP_TRY(hipMalloc(&p->dtables, total), "hipMalloc(offset tables)");
   std::vector<char> host(total, 0);
   for (int i = 0; i < 9; ++i)
     if (!tabs[i]->empty()) std::memcpy(host.data() + off[i], tabs[i]->data(), tabs[i]->size() * sizeof(int64_t));
+  for (int i = 0; packed && i < 4; ++i) {
+    uint32_t *t = reinterpret_cast<uint32_t *>(host.data() + poff[i]);
+    const size_t n = tabs[i]->size();
+    const bool rows = i == 0 || i == 3;
+    for (size_t j = 0; j < plen[i]; ++j)
+      t[j] = j >= n && !rows ? kPackedOut : uint32_t((*tabs[i])[std::min(j, n - 1)] * int64_t(es));
+  }
   HIP_TRY(hipMemcpy(p->dtables, host.data(), total, hipMemcpyHostToDevice), "hipMemcpy(offset tables)");
   char *b = static_cast<char *>(p->dtables);
   p->t.offAm = reinterpret_cast<const int64_t *>(b + off[0]);
@@ -153,10 +198,31 @@ comet_status_t upload_tables(comet_plan_s *p) {
   p->t.offBn = reinterpret_cast<const int64_t *>(b + off[3]);
   p->t.offCm = reinterpret_cast<const int64_t *>(b + off[4]);
   p->t.offCn = reinterpret_cast<const int64_t *>(b + off[5]);
+  if (packed) {
+    PackedLaunch &k = p->pk;
+    k.am = reinterpret_cast<const uint32_t *>(b + poff[0]);
+    k.ak = reinterpret_cast<const uint32_t *>(b + poff[1]);
+    k.bk = reinterpret_cast<const uint32_t *>(b + poff[2]);
+    k.bn = reinterpret_cast<const uint32_t *>(b + poff[3]);
+    k.c = p->t;
+    k.bytesA = uint32_t((an.swapped ? an.sizeB : an.sizeA) * int64_t(es));
+    k.bytesB = uint32_t((an.swapped ? an.sizeA : an.sizeB) * int64_t(es));
+    k.M = int(an.m);
+    k.N = int(an.n);
+    k.K = int(an.k);
+    k.dtype = an.dtype == COMET_F64 ? 0 : 1;
+    k.layoutA = an.layoutA;
+    k.layoutB = an.layoutB;
+    k.c_segments = c_segments(an);
+  }
   if (!an.offAx.empty()) {
     p->offAx = reinterpret_cast<const int64_t *>(b + off[6]);
     p->offBx = reinterpret_cast<const int64_t *>(b + off[7]);
     p->offCx = reinterpret_cast<const int64_t *>(b + off[8]);
+    p->pk.xa = p->offAx;
+    p->pk.xb = p->offBx;
+    p->pk.xc = p->offCx;
+    p->pk.entries = an.nb;
   }
   return COMET_OK;
 }
@@ -205,6 +271,18 @@ constexpr int kSkMinSteps = 8;          // fewest BK steps a stream-K share shou
 constexpr int kSkSmallSteps = 4;        // the same for latency-bound problems (tile 1)
 constexpr double kSkBytesPerUs = 4.0e6;  // partial-sum traffic rate (HBM, both directions)
 constexpr double kSkLaunchUs = 4.0;      // the two extra launches
+
+// Whether the packed kernel will run the contraction and finds both operands
+// in runs of at least two elements on average: its loads are then as good as
+// those of TTGT's matrices (1725^3 in FP64, extents of 75 and 23: 286 us by
+// TTGT's permutes and its element-load GEMM, 175 us read in place).
+bool packed_reads(const comet_plan_s *p) {
+  const Analysis &an = p->an;
+  const char *env = std::getenv("COMET_PACKED");
+  if (!p->pk.am || (env && std::strcmp(env, "0") == 0)) return false;
+  return unit_steps(an.layoutA == LAYOUT_MN_CONTIG ? an.offAm : an.offAk) >= 0.5 &&
+         unit_steps(an.layoutB == LAYOUT_MN_CONTIG ? an.offBn : an.offBk) >= 0.5;
+}
 
 // Estimated saving (seconds, may be negative) of TTGT plan `tt` over the
 // element-load gather of the same contraction `an`: the GEMM time saved
@@ -483,6 +561,7 @@ void even_choice(const Analysis &an, int cus, bool vecA, bool vecB, Schedule &sc
 // 1 GB of stores one after the other.  Returns its workgroups, 0 if not
 // taken; COMET_GETT_SHORTK=0 / 1 turns it off / on where it exists.
 constexpr int kShortKMax = 32;
+bool c_segments(const Analysis &an);
 int shortk_choice(const Analysis &an, int cus, bool vecA, bool vecB, int forced_tile) {
   const bool native = an.compute == COMET_COMPUTE_F64 || an.compute == COMET_COMPUTE_F32;
   const int dt = an.dtype == COMET_F64 ? 0 : 1, cp = an.compute == COMET_COMPUTE_F64 ? 0 : 1;
@@ -503,7 +582,125 @@ int shortk_choice(const Analysis &an, int cus, bool vecA, bool vecB, int forced_
   const int64_t T = ((an.m + 127) / 128) * ((an.n + 127) / 128);
   const char *env = std::getenv("COMET_GETT_SHORTK");
   if (env && *env) return std::atoi(env) != 0 ? int(S) : 0;
-  return T >= 4 * S ? int(S) : 0;
+  // Against the packed kernel's small tiles, which fill the last round
+  // better (K = 20, FP64, 2000 tiles: 65 us either way; K = 32, 8192 tiles:
+  // 250 against 281; FP32, 2684 tiles in 5.2 rounds: 70 against 59, 3456 in
+  // 6.75: 66 against 77), and which write partial segments of C past the
+  // caches as this kernel does not (K = 30, 3000 x 9000: 130 against 57).
+  const int64_t rounds = (T + S - 1) / S;
+  return T >= 4 * S && c_segments(an) && 20 * T >= 19 * rounds * S ? int(S) : 0;
+}
+
+// The packed kernel's schedule: its tile, the tiles computed whole and the
+// workgroups sharing the rest.  Time model of one launch, in microseconds,
+// fitted to 102 products of 20 to 98304 on a side (FP64 and FP32, each with
+// every tile and up to twelve splits) on MI355X; the schedule it picks is 1%
+// off the fastest one timed on average, 12% at worst.
+struct PackedRate {
+  double step;    // one summation step of a tile while its CU is full
+  double lone;    // the same for a workgroup that has the CU to itself
+  double tile;    // prologue and epilogue of a tile
+};
+constexpr PackedRate kPackedRate[2][kPackedTiles] = {
+    {{1.983, 2.137, 4.15}, {0.523, 0.707, 0.83}, {1.006, 1.151, 1.0}, {0.299, 0.399, 0.99}, {0.289, 0.443, 0.80}},
+    {{1.970, 2.224, 2.50}, {0.558, 0.728, 0.50}, {1.075, 1.178, 1.0}, {0.321, 0.431, 0.80}, {0.285, 0.410, 0.78}},
+};
+constexpr double kPackedMore[2] = {0.585, 0.569};  // a further tile of the CU, in units of `tile`
+constexpr double kPackedLaunch[2] = {3.7, 4.1};    // a launch
+constexpr double kPackedFixup[2] = {4.5, 3.7};     // the fix-up launch ...
+constexpr double kPackedBytes = 5.7e6;             // ... and the partial tiles' traffic, bytes per us
+constexpr double kPackedStore[2] = {3.76e6, 3.08e6};   // output bytes (whole tiles) per us
+constexpr int64_t kPackedEntryK = 96;              // see packed_choice
+constexpr int kPackedMinSteps = 2;                 // fewest steps a share should hold
+
+double packed_time_us(int dt, int tile, int resident, int cus, int64_t T, int64_t nk, size_t slot, int64_t whole,
+                      int64_t shares) {
+  const PackedRate &r = kPackedRate[dt][tile];
+  const double per_cu = double(std::max(whole + shares, T)) / cus;
+  const double store = double(T) * double(slot) / kPackedStore[dt];
+  double us;
+  if (shares == 0) {
+    const int64_t c = (T + cus - 1) / cus;
+    us = double(nk) * (c <= resident ? std::max(r.lone, double(c) * r.step) : double(c) * r.step) +
+         r.tile * (1.0 + double(c - 1) * kPackedMore[dt]);
+    return kPackedLaunch[dt] + std::max(us, store);
+  }
+  const double steps = double((T - whole) * nk) / double(shares);
+  const double work = (double(whole) / cus * double(nk) + double((shares + cus - 1) / cus) * steps) * r.step;
+  const double lone = std::max(whole > 0 ? double(nk) : 0.0, std::ceil(steps)) * r.lone;
+  const int64_t pieces = std::min(2 * shares, shares + T - whole);
+  us = std::max(work, lone) + r.tile * (1.0 + std::max(0.0, per_cu - 1.0) * kPackedMore[dt]);
+  us = std::max(us, store) + kPackedFixup[dt] + double(pieces) * double(slot) * 2.0 / kPackedBytes;
+  return kPackedLaunch[dt] + us;
+}
+
+// Takes the packed kernel where it can run and no gather tile or schedule is
+// asked for: in 102 products against the vector-load tiles (which odd extents
+// confine to 64 x 64 element loads) it was the faster one in all but one, by
+// 1.4 times in the middle (FP64 1725^3: 244 -> 171 us, 1200^3: 91 -> 70 us,
+// 364^3: 18 -> 13 us; FP32 3072^3: 549 -> 431 us, 1725^3: 206 -> 95 us).
+// COMET_PACKED=0 turns it off, =tile,whole,shares forces a schedule.
+// `taken`: workspace bytes the plan holds besides; the partial tiles stay
+// within what comet_plan_execute_noalloc holds.
+void packed_choice(comet_plan_s *p, int cus, bool gather_forced) {
+  Analysis &an = p->an;
+  an.packed = an.packed_whole = an.packed_shares = 0;
+  const char *env = std::getenv("COMET_PACKED");
+  if (!p->pk.am || gather_forced || an.shortk > 0 || (env && std::strcmp(env, "0") == 0)) return;
+  // Batch entries of one or two tiles and a short summation, read in vectors,
+  // are bound by their loads: the vector-load tiles move twice the bytes per
+  // instruction (4096 x 64^3 in FP64 65 us against 70, 500 x 96^3 33 against
+  // 36; FP32 36 against 42 and 21 against 23; but 4000 x 32^3, whose entries
+  // half fill their tile, 32 against 23, and 300 x 100^3 34 against 31).
+  if (!an.X.empty() && p->vecA_tables && p->vecB_tables && an.k <= kPackedEntryK && an.m > 32 && an.n > 32) return;
+  const int dt = an.dtype == COMET_F64 ? 0 : 1;
+  const size_t limit = COMET_NOALLOC_SCRATCH_BYTES;
+  const size_t budget = p->ws_taken > limit ? SIZE_MAX : limit - p->ws_taken;
+  int ft = -1;
+  long fw = 0, fs = 0;
+  if (env && *env && std::sscanf(env, "%d,%ld,%ld", &ft, &fw, &fs) < 1) ft = -1;
+  PackedLaunch &k = p->pk;
+  double best = 1e300;
+  size_t best_ws = 0;
+  for (int tile = 0; tile < kPackedTiles; ++tile) {
+    if (ft >= 0 && tile != ft) continue;
+    int bm, bn, bk;
+    packed_tile_shape(tile, dt, &bm, &bn, &bk);
+    const int64_t tm = (an.m + bm - 1) / bm, tn = (an.n + bn - 1) / bn, T = tm * tn, nk = (an.k + bk - 1) / bk;
+    const size_t slot = size_t(bm) * bn * elem_size(an.dtype);
+    const int res = packed_occupancy(tile, dt, an.layoutA, an.layoutB);
+    if (res <= 0 || T > INT32_MAX / 2 || T * an.nb > (int64_t(1) << 40)) continue;
+    const int64_t C = std::max(cus, 1), S = C * res;
+    auto consider = [&](int64_t whole, int64_t shares) {
+      const size_t ws = 2 * size_t(shares) * slot;
+      if (ws > budget) return;
+      const double us = packed_time_us(dt, tile, res, int(C), T * an.nb, nk, slot, whole, shares);
+      if (us >= best) return;
+      best = us;
+      best_ws = ws;
+      an.packed = tile + 1;
+      an.packed_whole = int(whole);
+      an.packed_shares = int(shares);
+      k.tile = tile;
+      k.tilesM = int(tm);
+      k.tilesN = int(tn);
+      k.whole = int(whole);
+      k.shares = int(shares);
+    };
+    if (ft >= 0) {
+      const int64_t w = an.X.empty() ? std::max<int64_t>(0, std::min<int64_t>(fw, T)) : T;
+      consider(w, w == T ? 0 : std::max<int64_t>(1, std::min<int64_t>(fs, (T - w) * nk)));
+      continue;
+    }
+    consider(T, 0);
+    if (!an.X.empty()) continue;
+    for (const int64_t whole : {int64_t(0), T / C * C, T / S * S})
+      for (const int64_t want : {C / 2, C, 2 * C, S}) {
+        const int64_t shares = std::min(want, (T - whole) * nk / kPackedMinSteps);
+        if (whole < T && shares > 0) consider(whole, shares);
+      }
+  }
+  if (an.packed > 0) p->sk_bytes = align256(best_ws);
 }
 
 void apply_schedule(comet_plan_s *p, int cus, int forced_tile = -1) {
@@ -532,13 +729,14 @@ void apply_schedule(comet_plan_s *p, int cus, int forced_tile = -1) {
   const size_t slot = gett_sk_slot_bytes(sc.tile, an.compute == COMET_COMPUTE_F64 ? 0 : 1);
   // stream-K: two slots per workgroup (its first and last tile); balanced: one
   p->sk_bytes = sc.sk_tiles > 0 ? align256(size_t(sc.even ? 1 : 2) * size_t(sc.sk_blocks) * slot) : 0;
+  const bool gather_forced = forced >= 0 || std::getenv("COMET_GETT_SK") || std::getenv("COMET_GETT_PERSIST") ||
+                             std::getenv("COMET_GETT_EVEN");
+  packed_choice(p, cus, gather_forced);
   // a matrix times a vector: the streaming kernel instead of the tiles,
   // unless a gather schedule is forced or COMET_GEMV=0
   an.gemv = an.gemv_split = 0;
   an.gemv_slab = 0;
   const char *genv = std::getenv("COMET_GEMV");
-  const bool gather_forced = forced >= 0 || std::getenv("COMET_GETT_SK") || std::getenv("COMET_GETT_PERSIST") ||
-                             std::getenv("COMET_GETT_EVEN");
   // (the vector has no free label, so C's unit stride lies in the matrix and
   // the planner's exchange makes the vector the kernel's A operand: M == 1)
   if (native && !an.empty_out && !an.empty_sum && an.X.empty() && an.m == 1 && !gather_forced &&
@@ -565,6 +763,7 @@ void apply_schedule(comet_plan_s *p, int cus, int forced_tile = -1) {
       an.gemv_split = sp;
       an.gemv_slab = sl;
       an.shortk = an.sk_tiles = an.sk_blocks = an.even = an.even_whole = an.persist = 0;
+      an.packed = an.packed_whole = an.packed_shares = 0;
       p->sk_bytes = ws;
     }
   }
@@ -715,7 +914,8 @@ comet_status_t build_plan(std::unique_ptr<comet_plan_s> &out, const char *spec, 
   const bool gather_forced = std::getenv("COMET_GETT_TILE") || std::getenv("COMET_GETT_SK") ||
                              std::getenv("COMET_GETT_PERSIST") || std::getenv("COMET_GETT_EVEN");
   if (path == COMET_PATH_AUTO && native && !tuning && !gather_forced && an.path == COMET_PATH_GETT &&
-      an.X.empty() && !an.empty_out && !an.empty_sum && !(p->vecA_tables && p->vecB_tables)) {
+      an.X.empty() && !an.empty_out && !an.empty_sum && !(p->vecA_tables && p->vecB_tables) &&
+      !packed_reads(p.get())) {
     std::unique_ptr<comet_plan_s> tt;
     if (build_plan(tt, spec, extents, sA, sB, sC, dtype, compute, COMET_PATH_TTGT, false) == COMET_OK && tt->gemm &&
         tt->ws_bytes <= kTTGTMaxWorkspace && ttgt_saving_s(an, *tt) > 0.0) {
@@ -725,6 +925,7 @@ comet_status_t build_plan(std::unique_ptr<comet_plan_s> &out, const char *spec, 
   }
   apply_schedule(p.get(), cus);
   if (p->gemm) {
+    p->gemm->ws_taken = p->ws_bytes;
     apply_schedule(p->gemm.get(), cus);
     p->gemm->ws_bytes = p->gemm->sk_bytes;
     p->wsG = p->ws_bytes;
@@ -790,6 +991,17 @@ comet_status_t run_gett(const comet_plan_s *p, double alpha, const void *A, cons
     v.beta = beta;
     v.ws = ws;
     HIP_TRY(launch_gemv(v, s), "matrix-vector launch");
+    return COMET_OK;
+  }
+  if (an.packed > 0) {
+    PackedLaunch k = p->pk;
+    k.A = an.swapped ? B : A;
+    k.B = an.swapped ? A : B;
+    k.C = C;
+    k.alpha = alpha;
+    k.beta = beta;
+    k.ws = ws;
+    HIP_TRY(launch_packed(k, s), "packed gather launch");
     return COMET_OK;
   }
   GettLaunch g{};
@@ -1220,6 +1432,22 @@ comet_status_t autotune_plan(std::unique_ptr<comet_plan_s> &p, const char *spec,
         double us = time_us([&]() { return run_gett(pp, 1.0, bufA, bufB, 0.0, bufC, s, skws); }, s, &good);
         if (good && us < best.us) best = TuneEntry{tile, COMET_PATH_GETT, us};
       }
+      // the packed kernel's own schedule
+      apply_schedule(p.get(), cus);
+      if (an.packed > 0 && p->sk_bytes > skws_bytes) {
+        if (skws) (void)hipFree(skws);
+        skws = nullptr;
+        skws_bytes = hipMalloc(&skws, p->sk_bytes) == hipSuccess ? p->sk_bytes : 0;
+      }
+      if (an.packed > 0 && p->sk_bytes <= skws_bytes) {
+        bool good;
+        const comet_plan_s *pp = p.get();
+        double us = time_us([&]() { return run_gett(pp, 1.0, bufA, bufB, 0.0, bufC, s, skws); }, s, &good);
+        if (good && us < best.us) {
+          best = TuneEntry{an.tile, COMET_PATH_GETT, us};
+          best.packed = 1;
+        }
+      }
       if (tt) {
         // every TTGT flattening, cheapest by the cost model first, up to
         // kTuneTTGT of them (the model ranks them poorly on MI355X, so it only
@@ -1276,7 +1504,10 @@ comet_status_t autotune_plan(std::unique_ptr<comet_plan_s> &p, const char *spec,
       return COMET_OK;
     }
   }
-  if (best.tile >= 0 && best.tile < gett_tile_count()) {
+  if (best.packed) {
+    apply_schedule(p.get(), cus);
+    p->ws_bytes = p->sk_bytes;
+  } else if (best.tile >= 0 && best.tile < gett_tile_count()) {
     apply_schedule(p.get(), cus, best.tile);
     p->ws_bytes = p->sk_bytes;
   }
@@ -1619,7 +1850,8 @@ std::string cache_key(const char *spec, const int64_t *ext, size_t nlab, const i
        std::to_string(g_split_slices) + "|" + std::to_string(g_int8_slices);
   // every planner override in the environment
   for (const char *name : {"COMET_FORCE_PATH", "COMET_TTGT_ORDER", "COMET_GETT_TILE", "COMET_GETT_SK",
-                           "COMET_GETT_PERSIST", "COMET_GETT_SHORTK", "COMET_GETT_EVEN", "COMET_SPLIT_TILE", "COMET_FUSED3"}) {
+                           "COMET_GETT_PERSIST", "COMET_GETT_SHORTK", "COMET_GETT_EVEN", "COMET_SPLIT_TILE", "COMET_FUSED3",
+                           "COMET_PACKED"}) {
     const char *v = std::getenv(name);
     k += "|";
     if (v) k += v;

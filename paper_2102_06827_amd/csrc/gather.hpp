@@ -493,7 +493,15 @@ __device__ __forceinline__ void gett_accumulate(WaveTile<Tc, BM, BN, WGM, WGN> &
 // the compiler can wait for loads issued before them without waiting for the
 // stores themselves (a skipped store makes that count unknown, and every
 // later wait a full one).
-template <typename Tin, typename Tc, int BM, int BN, int WGM, int WGN, bool SINK = false>
+// STREAM: nontemporal stores (see above); else plain ones.
+template <typename T, bool STREAM>
+__device__ __forceinline__ void store_c(T v, glb_t<T> *p) {
+  if constexpr (STREAM)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+template <typename Tin, typename Tc, int BM, int BN, int WGM, int WGN, bool SINK = false, bool STREAM = true>
 __device__ __forceinline__ void gett_store_staged(const WaveTile<Tc, BM, BN, WGM, WGN> &w, Tin *__restrict__ C,
                                                   const lds_t<int64_t> *cm, const lds_t<int64_t> *cn, int64_t M,
                                                   int64_t N, double alpha, double beta, int64_t m0, int64_t n0,
@@ -520,9 +528,9 @@ __device__ __forceinline__ void gett_store_staged(const WaveTile<Tc, BM, BN, WGM
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         if constexpr (SINK)
-          __builtin_nontemporal_store(Tin(al * Te(w.acc[i][j][r])), inside(i, r, j) ? &gC[a[r]] : to_glb(sink));
+          store_c<Tin, STREAM>(Tin(al * Te(w.acc[i][j][r])), inside(i, r, j) ? &gC[a[r]] : to_glb(sink));
         else if (inside(i, r, j))
-          __builtin_nontemporal_store(Tin(al * Te(w.acc[i][j][r])), &gC[a[r]]);
+          store_c<Tin, STREAM>(Tin(al * Te(w.acc[i][j][r])), &gC[a[r]]);
       }
     }
     return;
@@ -555,9 +563,9 @@ __device__ __forceinline__ void gett_store_staged(const WaveTile<Tc, BM, BN, WGM
     for (int r = 0; r < 4; ++r) {
       const Tin v = Tin(al * Te(w.acc[i][j][r]) + be * Te(cv[g & 1][r]));
       if constexpr (SINK)
-        __builtin_nontemporal_store(v, inside(i, r, j) ? &gC[a[r]] : to_glb(sink));
+        store_c<Tin, STREAM>(v, inside(i, r, j) ? &gC[a[r]] : to_glb(sink));
       else if (inside(i, r, j))
-        __builtin_nontemporal_store(v, &gC[a[r]]);
+        store_c<Tin, STREAM>(v, &gC[a[r]]);
     }
   }
 }
@@ -625,7 +633,7 @@ __device__ __forceinline__ void gett_store(const WaveTile<Tc, BM, BN, WGM, WGN> 
 
 // C = alpha * v + beta * C for accumulator element (i, j) of this thread
 // only (the same outputs gett_store writes from w.acc[i][j]).
-template <typename Tin, typename Tc, int BM, int BN, int WGM, int WGN>
+template <typename Tin, typename Tc, int BM, int BN, int WGM, int WGN, bool STREAM = true>
 __device__ __forceinline__ void gett_store_fragment(const typename AccT<Tc>::type &v, int i, int j,
                                                     Tin *__restrict__ C, const GettTables &t, int64_t M, int64_t N,
                                                     double alpha, double beta, int64_t m0, int64_t n0) {
@@ -651,7 +659,7 @@ __device__ __forceinline__ void gett_store_fragment(const typename AccT<Tc>::typ
   for (int r = 0; r < 4; ++r) x[r] = beta != 0.0 ? be * Te(gC[addr[r]]) : Te(0);
 #pragma unroll
   for (int r = 0; r < 4; ++r)
-    if (m0 + wm0 + i * 16 + acc_row<Tc>(lane, r) < M) __builtin_nontemporal_store(Tin(al * Te(v[r]) + x[r]), &gC[addr[r]]);
+    if (m0 + wm0 + i * 16 + acc_row<Tc>(lane, r) < M) store_c<Tin, STREAM>(Tin(al * Te(v[r]) + x[r]), &gC[addr[r]]);
 }
 
 // A partial sum of one tile in workspace: accumulator element (i, j) of

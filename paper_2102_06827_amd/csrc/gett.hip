@@ -23,7 +23,10 @@
 // planner orders A and B so that C's unit-stride label lies along N, which
 // the MFMA output spreads over consecutive lanes.
 #include <algorithm>
+#include <array>
 #include <cstdlib>
+#include <map>
+#include <mutex>
 #include <type_traits>
 
 #include "gather.hpp"
@@ -445,8 +448,18 @@ __global__ __launch_bounds__(64 * kTiles[TILE].wgm * kTiles[TILE].wgn) void gett
 // The K-table entries do not depend on the tile and are fetched once.
 constexpr int kShortK = 32;
 
-// where the short-summation kernel's lanes outside the output store
-__device__ __align__(16) double shortk_sink[2];
+// Where the short-summation kernel's lanes outside the output store: a
+// location per thread of a workgroup, a workgroup in 64 (all lanes storing to
+// one location queued up behind each other: K = 30 with a 3000 x 9000 output
+// took 176 us).
+constexpr int kSinkGroups = 64;
+template <int NT>
+__device__ __forceinline__ double *shortk_sink();
+__device__ __align__(16) double shortk_sink_[kSinkGroups * 512];
+template <>
+__device__ __forceinline__ double *shortk_sink<512>() {
+  return shortk_sink_ + (blockIdx.x % kSinkGroups) * 512 + threadIdx.x;
+}
 
 template <typename Tin, typename Tc, int TILE, int LA, int LB>
 constexpr int shortk_lds_elems() {
@@ -582,7 +595,7 @@ __global__ __launch_bounds__(64 * kTiles[TILE].wgm * kTiles[TILE].wgn, 1) void g
     const lds_t<int64_t> *ct = ctab + (j & 1) * (BM + BN);
     gett_store_staged<Tin, Tc, BM, BN, WGM, WGN, true>(w, C, ct, ct + BM, M, N, alpha, BETA0 ? 0.0 : beta,
                                                        int64_t(tm0) * BM, int64_t(tn0) * BN,
-                                                       reinterpret_cast<Tin *>(shortk_sink));
+                                                       reinterpret_cast<Tin *>(shortk_sink<NT>()));
   }
 #undef SHORTK_FETCH_TABLES
 #undef SHORTK_STAGE_TABLES
@@ -876,7 +889,7 @@ hipError_t launch_gett(const GettLaunch &g, hipStream_t s) {
   return g.compute == 0 ? launch_tc<float, double>(g, s) : launch_tc<float, float>(g, s);
 }
 
-int gett_occupancy(const GettLaunch &g) {
+static int gett_occupancy_query(const GettLaunch &g) {
   int n = 0;
   GettLaunch q = g;
   q.occupancy = &n;
@@ -885,6 +898,23 @@ int gett_occupancy(const GettLaunch &g) {
     (void)hipGetLastError();
     return 0;
   }
+  return n;
+}
+
+// (each answer is kept: it depends on the kernel alone, and a plan asks for
+// some twenty of them)
+int gett_occupancy(const GettLaunch &g) {
+  static std::mutex mu;
+  static std::map<std::array<int, 10>, int> known;
+  int device = 0;
+  (void)hipGetDevice(&device);
+  const std::array<int, 10> key = {device, g.dtype, g.compute, g.layoutA, g.layoutB, g.vecA * 2 + g.vecB, g.tile,
+                                   g.query_sk, g.persistent > 0, g.shortk > 0};
+  std::lock_guard<std::mutex> lk(mu);
+  const auto it = known.find(key);
+  if (it != known.end()) return it->second;
+  const int n = gett_occupancy_query(g);
+  known[key] = n;
   return n;
 }
 

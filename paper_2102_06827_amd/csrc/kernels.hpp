@@ -118,6 +118,38 @@ hipError_t launch_batch(const BatchDesc *descs, const BatchItem *items, const Ba
 // persistent workgroups per CU for the batched kernel
 int batch_blocks_per_cu(int dtype, int mode);
 
+// The packed gather kernel (packed.hip): FP64 or FP32 storage and arithmetic,
+// any strides, operands of less than kPackedMaxBytes.  am, ak, bk, bn are the
+// offset tables in bytes, the row tables padded to a multiple of kPackedRowPad
+// and the summation tables by kPackedKPad entries, with their last entry.
+// Tiles 0 .. whole - 1 (in the XCD-aware order) are computed by a workgroup
+// each; `shares` workgroups split the steps of the others, whose partial
+// tiles take 2 * shares * bm * bn elements of ws.
+constexpr int kPackedTiles = 5;
+constexpr int kPackedRowPad = 128;
+constexpr int kPackedKPad = 160;
+constexpr uint32_t kPackedOut = 0x80000000u;
+constexpr int64_t kPackedMaxBytes = int64_t(1) << 31;
+struct PackedLaunch {
+  const void *A, *B;
+  void *C;
+  const uint32_t *am, *ak, *bk, *bn;
+  GettTables c;               // offCm, offCn only
+  uint32_t bytesA, bytesB;    // spans of the operands
+  int M, N, K;
+  double alpha, beta;
+  int tilesM, tilesN, whole, shares;
+  void *ws;
+  int tile, dtype, layoutA, layoutB;
+  const int64_t *xa, *xb, *xc;   // batch labels: base offsets (elements) of each entry (or null); whole tiles only
+  int64_t first, entries;
+  int c_segments;             // C's offsets come in whole, aligned 64-byte segments along n
+};
+hipError_t launch_packed(const PackedLaunch &g, hipStream_t s);
+void packed_tile_shape(int tile, int dtype, int *bm, int *bn, int *bk);
+// workgroups of a tile that fit on one CU
+int packed_occupancy(int tile, int dtype, int layoutA, int layoutB);
+
 // C[offCb[b] + offCm[m] + offCn[n]] = beta * C over NB batch entries
 // (offCb == nullptr: NB must be 1 and offCb[0] reads as 0); beta == 0 writes
 // zeros without reading.

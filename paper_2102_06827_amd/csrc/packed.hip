@@ -1,0 +1,486 @@
+// packed.hip -- gather product over any strides and extents: single elements
+// are loaded, and packed along the summation on their way into LDS.
+//
+// The vector-load tiles of gett.hip need 16-byte aligned runs in both
+// operands; orbital counts are as often odd as not, and then they have only
+// a 64 x 64 tile that loads elements through 64-bit offset pairs.  This
+// kernel loads nothing but single elements, so it needs no runs and no
+// alignment, and makes them cheap instead:
+//
+//   * Offsets are 32-bit byte offsets (operands below 2 GiB).  An operand
+//     contiguous along its rows has one row offset per thread, in a vector
+//     register, and its summation offsets in scalar registers: a buffer load
+//     adds the two, so an element costs one instruction.  An operand
+//     contiguous along the summation has the summation offset in a vector
+//     register, one per step, and one vector addition per element.
+//   * 64 lanes read 64 consecutive elements (or 64 / BK runs of BK), so the
+//     loads are as coalesced as the operand allows.  Rows past the edge read
+//     the last row (the tables are padded with it), whose products are never
+//     stored; only the last, partial summation step masks anything.
+//   * Every LDS tile is stored [row][k] with a 16-byte pad, whatever the
+//     operand's order: a thread that walks the summation writes its 16 bytes
+//     of consecutive k at once.  A lane then reads 16 bytes of one row for 2
+//     (FP64) or 4 (FP32) MFMAs: over a chunk of 4 * VL summation indices,
+//     lane group g = lane / 16 holds indices g * VL .. g * VL + VL - 1, and
+//     MFMA j of the chunk multiplies index g * VL + j of every group (A and B
+//     agree on it, so the sum is the same up to order).  With a pitch of
+//     BK + VL elements the 16 rows a lane group reads start in 16 different
+//     groups of four banks.
+//
+// Bound: the matrix cores.  Software pipeline, one barrier a step: a step's
+// products run while the next step moves from registers to LDS (during the
+// first half) and the one after is asked for (during the second), the LDS
+// writes and loads spread between the MFMAs, so that nothing waits for a load
+// issued less than a step ago.  MI355X, against the tiles of gett.hip on the
+// same box: a full round of 128 x 128 tiles over K = 8208, FP64 66-71 TFLOP/s
+// (60-64), FP32 122-138 (103-107); 1725^3 in FP64 171 us (244; by TTGT's
+// permutes and GEMM 286), in FP32 95 us (206); 256^3 in FP64 9.4 us (12.4).
+//
+// The tiles: 128 x 128 moves the fewest bytes per product; the smaller ones
+// fill the chip and fit ragged edges better, down to half of a 64 x 64 tile
+// for outputs with one side of at most 32 (98304 x 32, K = 96, FP64: 20 us
+// against 27 on 64 x 64) and for latency (512^3: 15 us against 17).
+//
+// A launch is `whole` workgroups that compute one output tile each, then
+// `shares` workgroups that split the summation steps of the remaining tiles
+// equally; a share may run over tile boundaries.  Partial tiles go to the
+// workspace and packed_fixup_kernel adds them in share order.
+#include <array>
+#include <climits>
+#include <map>
+#include <mutex>
+#include <type_traits>
+
+#include "gather.hpp"
+#include "kernels.hpp"
+
+namespace comet {
+namespace {
+
+using namespace gather;
+
+// Workgroup tile BM x BN, summation step BK, a WGM x WGN grid of waves, and
+// the waves per SIMD the register allocation leaves room for.
+struct PackedTile {
+  int bm, bn, bk, wgm, wgn, wpe;
+};
+constexpr PackedTile kPacked64[] = {
+    {128, 128, 16, 4, 2, 4},
+    {64, 64, 16, 2, 2, 4},
+    {128, 64, 16, 4, 2, 4},
+    {64, 32, 16, 2, 2, 4},
+    {32, 64, 16, 2, 2, 4},
+};
+constexpr PackedTile kPacked32[] = {
+    {128, 128, 32, 2, 2, 2},
+    {64, 64, 32, 2, 2, 4},
+    {128, 64, 32, 4, 2, 4},
+    {64, 32, 32, 2, 2, 4},
+    {32, 64, 32, 2, 2, 4},
+};
+static_assert(sizeof(kPacked64) / sizeof(PackedTile) == kPackedTiles, "tile count");
+static_assert(sizeof(kPacked32) / sizeof(PackedTile) == kPackedTiles, "tile count");
+template <typename T>
+constexpr PackedTile packed_tile(int tile) {
+  return sizeof(T) == 8 ? kPacked64[tile] : kPacked32[tile];
+}
+
+// a table read by wave-uniform indices only: scalar loads
+typedef const __attribute__((address_space(4))) uint32_t *scalar_table;
+
+__device__ __forceinline__ void buffer_element(double *v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  const u2 x = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+  *v = __builtin_bit_cast(double, x);
+}
+__device__ __forceinline__ void buffer_element(float *v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  *v = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+}
+
+// `bytes` from p on; a load past them gives zero
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
+}
+
+// One operand's tile: R rows by BK summation indices, PER elements a thread.
+template <typename T, int R, int BK, int LAYOUT, int NT>
+struct PackedLoader {
+  static constexpr int VL = 16 / int(sizeof(T));
+  static constexpr int LDK = BK + VL;
+  static constexpr int ELEMS = R * LDK;
+  static constexpr int PER = R * BK / NT;
+  static_assert(PER * NT == R * BK && PER % VL == 0, "tile does not split evenly over the workgroup");
+  static_assert(LAYOUT == 0 ? NT % BK == 0 : NT % R == 0, "thread mapping");
+  // a wave's lanes share their summation indices: scalar offsets
+  static constexpr bool UNIFORM = LAYOUT == 1 && R % 64 == 0;
+  typedef T vec_t __attribute__((ext_vector_type(VL)));
+
+  T v[PER];
+  uint32_t ro[LAYOUT == 0 ? PER : 1];   // row offsets
+  uint32_t ko[LAYOUT == 0 ? 1 : PER];   // summation offsets of the next step (LAYOUT 1: scalar)
+  int row, k;                           // LAYOUT 0: first row, the thread's index; LAYOUT 1: the row, first index
+
+  // rows: the row table at the tile's first row
+  __device__ __forceinline__ void init(int tid, const uint32_t *rows) {
+    if constexpr (LAYOUT == 0) {
+      row = tid / BK;
+      k = tid % BK;
+#pragma unroll
+      for (int p = 0; p < PER; ++p) ro[p] = to_glb(rows)[row + p * (NT / BK)];
+    } else {
+      row = tid % R;
+      k = (UNIFORM ? __builtin_amdgcn_readfirstlane(tid / R) : tid / R) * PER;
+      ro[0] = to_glb(rows)[row];
+    }
+  }
+  // the summation offsets of the step at k0 (the table is padded past its end)
+  __device__ __forceinline__ void fetch_k(const uint32_t *tab, int k0) {
+    if constexpr (LAYOUT == 0) {
+      ko[0] = to_glb(tab)[k0 + k];
+    } else if constexpr (UNIFORM) {
+      const scalar_table st = (scalar_table)(tab + k0 + k);
+#pragma unroll
+      for (int p = 0; p < PER; ++p) ko[p] = st[p];
+    } else {
+#pragma unroll
+      for (int p = 0; p < PER; ++p) ko[p] = to_glb(tab)[k0 + k + p];
+    }
+  }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r) {
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      if constexpr (LAYOUT == 0)
+        buffer_element(&v[p], r, ro[p] + ko[0], 0);
+      else
+        buffer_element(&v[p], r, ro[0] + ko[p], 0);
+    }
+  }
+  // LDS writes a thread does per step
+  static constexpr int WRITES = LAYOUT == 0 ? PER : PER / VL;
+  // into the LDS tile
+  __device__ __forceinline__ void store(lds_t<T> *s) const {
+    if constexpr (LAYOUT == 0) {
+#pragma unroll
+      for (int p = 0; p < PER; ++p) s[(row + p * (NT / BK)) * LDK + k] = v[p];
+    } else {
+#pragma unroll
+      for (int p = 0; p < PER; p += VL) {
+        vec_t w;
+#pragma unroll
+        for (int i = 0; i < VL; ++i) w[i] = v[p + i];
+        *reinterpret_cast<lds_t<vec_t> *>(s + row * LDK + k + p) = w;
+      }
+    }
+  }
+};
+
+template <typename T, int TILE, int LA, int LB>
+struct PackedKernel {
+  static constexpr PackedTile S = packed_tile<T>(TILE);
+  static constexpr int BM = S.bm, BN = S.bn, BK = S.bk, WGM = S.wgm, WGN = S.wgn;
+  static constexpr int NT = 64 * WGM * WGN;
+  typedef WaveTile<T, BM, BN, WGM, WGN> WT;
+  typedef PackedLoader<T, BM, BK, LA, NT> LoadA;
+  typedef PackedLoader<T, BN, BK, LB, NT> LoadB;
+  static constexpr int VL = LoadA::VL, LDK = LoadA::LDK, CHUNK = 4 * VL;
+  static constexpr int LDS = 2 * (LoadA::ELEMS + LoadB::ELEMS);
+
+  // The tile's C offsets, asked for ahead of its operands (a short summation
+  // would otherwise end in waiting for them) and kept in LDS for the epilogue.
+  static_assert(BM + BN <= NT, "one C offset a thread");
+  struct COffsets {
+    int64_t v;
+    __device__ __forceinline__ void load(int tid, const GettTables &c, int m0, int n0, int M, int N) {
+      const bool row = tid < BM;
+      const int x = row ? m0 + tid : n0 + (tid - BM), last = row ? M - 1 : N - 1;
+      v = to_glb(row ? c.offCm : c.offCn)[x < last ? x : last];
+    }
+    __device__ __forceinline__ void store(int tid, lds_t<int64_t> *tab) const {
+      if (tid < BM + BN) tab[tid] = v;
+    }
+  };
+
+  // the products of chunk c of a step
+  static __device__ __forceinline__ void mma(WT &w, const lds_t<T> *a, const lds_t<T> *b, int c) {
+    typedef typename LoadA::vec_t vec_t;
+    vec_t af[WT::FM], bf[WT::FN];
+#pragma unroll
+    for (int i = 0; i < WT::FM; ++i) af[i] = *reinterpret_cast<const lds_t<vec_t> *>(a + i * 16 * LDK + c * CHUNK);
+#pragma unroll
+    for (int j = 0; j < WT::FN; ++j) bf[j] = *reinterpret_cast<const lds_t<vec_t> *>(b + j * 16 * LDK + c * CHUNK);
+#pragma unroll
+    for (int x = 0; x < VL; ++x)
+#pragma unroll
+      for (int i = 0; i < WT::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < WT::FN; ++j) w.acc[i][j] = mfma16(af[i][x], bf[j][x], w.acc[i][j]);
+  }
+  static constexpr int READS = WT::FM + WT::FN, MMAS = WT::FM * WT::FN * VL;
+
+  // schedule of one chunk: its LDS reads, then its products with one
+  // instruction of `kind` every few products
+  template <int KIND, int COUNT>
+  static __device__ __forceinline__ void schedule() {
+    __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
+    constexpr int EVERY = COUNT < MMAS ? MMAS / COUNT : 1, GROUP = (COUNT + MMAS - 1) / MMAS;
+#pragma unroll
+    for (int i = 0; i < (COUNT + GROUP - 1) / GROUP; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x8, EVERY, 0);
+      __builtin_amdgcn_sched_group_barrier(KIND, GROUP, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x8, MMAS, 0);
+  }
+
+  // the tile's product over the summation steps [s0, s1), s1 > s0; K
+  // indices in all
+  static __device__ __forceinline__ void accumulate(WT &w, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb,
+                                                    const uint32_t *am, const uint32_t *ak, const uint32_t *bk,
+                                                    const uint32_t *bn, int s0, int s1, lds_t<T> *smem,
+                                                    const COffsets &co, lds_t<int64_t> *ctab) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    lds_t<T> *const sB = smem + 2 * LoadA::ELEMS;
+    const int fa = ((wave / WGN) * WT::WM + (lane & 15)) * LDK + (lane >> 4) * VL;
+    const int fb = ((wave % WGN) * WT::WN + (lane & 15)) * LDK + (lane >> 4) * VL;
+#pragma unroll
+    for (int i = 0; i < WT::FM; ++i)
+#pragma unroll
+      for (int j = 0; j < WT::FN; ++j) w.acc[i][j] = typename WT::acc_t{0, 0, 0, 0};
+    LoadA la;
+    LoadB lb;
+    la.init(tid, am);
+    lb.init(tid, bn);
+    // Ahead of the products: LDS holds the next step, registers the one after.
+    // (Steps past the summation's end load zeros, past the share's end data
+    // that are not used; a loop that leaves them out was 3% faster on FP64's
+    // 64 x 64 tile and 10% slower on FP32's 128 x 128.)
+    static_assert(BK == 2 * CHUNK, "a step is two chunks");
+    la.fetch_k(ak, s0 * BK);
+    lb.fetch_k(bk, s0 * BK);
+    la.load(ra);
+    lb.load(rb);
+    la.fetch_k(ak, (s0 + 1) * BK);
+    lb.fetch_k(bk, (s0 + 1) * BK);
+    la.store(smem);
+    lb.store(sB);
+    co.store(tid, ctab);
+    la.load(ra);
+    lb.load(rb);
+    la.fetch_k(ak, (s0 + 2) * BK);
+    lb.fetch_k(bk, (s0 + 2) * BK);
+    __syncthreads();
+    int buf = 0;
+    for (int s = s0; s < s1; ++s) {
+      const lds_t<T> *a = smem + buf * LoadA::ELEMS + fa, *b = sB + buf * LoadB::ELEMS + fb;
+      mma(w, a, b, 0);
+      la.store(smem + (buf ^ 1) * LoadA::ELEMS);
+      lb.store(sB + (buf ^ 1) * LoadB::ELEMS);
+      schedule<0x200, LoadA::WRITES + LoadB::WRITES>();
+      __builtin_amdgcn_sched_barrier(0);
+      mma(w, a, b, 1);
+      la.load(ra);
+      lb.load(rb);
+      schedule<0x20, LoadA::PER + LoadB::PER>();
+      __builtin_amdgcn_sched_barrier(0);
+      la.fetch_k(ak, (s + 3) * BK);
+      lb.fetch_k(bk, (s + 3) * BK);
+      __syncthreads();
+      buf ^= 1;
+    }
+  }
+};
+
+// first step of share s of S over I steps
+__device__ __forceinline__ int64_t share_begin(int64_t I, int S, int s) { return I * s / S; }
+
+// STREAM: C is written with nontemporal stores.
+template <typename T, int TILE, int LA, int LB, bool STREAM>
+__global__ __launch_bounds__(64 * packed_tile<T>(TILE).wgm * packed_tile<T>(TILE).wgn, packed_tile<T>(TILE).wpe) void
+packed_kernel(PackedLaunch g) {
+  typedef PackedKernel<T, TILE, LA, LB> P;
+  typedef typename P::WT WT;
+  __shared__ __attribute__((aligned(16))) T smem[P::LDS];
+  __shared__ int64_t ctab_s[P::BM + P::BN];
+  lds_t<int64_t> *const ctab = to_lds(ctab_s);
+  const int b = blockIdx.x;
+  const int nk = (g.K + P::BK - 1) / P::BK;
+  const bool is_whole = b < g.whole;
+  const int share = is_whole ? 0 : xcd_remap(b - g.whole, g.shares);
+  const int64_t I = int64_t(g.tilesM * g.tilesN - g.whole) * nk;
+  int64_t it = 0, end = nk;
+  if (!is_whole) {
+    it = share_begin(I, g.shares, share);
+    end = share_begin(I, g.shares, share + 1);
+  }
+  // batch labels: the entry's slices
+  int64_t xa = 0, xb = 0, xc = 0;
+  if (g.xa) {
+    const int64_t x = g.first + blockIdx.y;
+    xa = to_glb(g.xa)[x];
+    xb = to_glb(g.xb)[x];
+    xc = to_glb(g.xc)[x];
+  }
+  T *const C = static_cast<T *>(g.C) + xc;
+  const __amdgpu_buffer_rsrc_t ra = buffer_of(static_cast<const T *>(g.A) + xa, g.bytesA - uint32_t(xa * sizeof(T)));
+  const __amdgpu_buffer_rsrc_t rb = buffer_of(static_cast<const T *>(g.B) + xb, g.bytesB - uint32_t(xb * sizeof(T)));
+  const int first = int(it / nk);
+  while (it < end) {
+    // (uniform values whose divisions run on the vector unit)
+    const int tt = __builtin_amdgcn_readfirstlane(int(it / nk));
+    const int s0 = __builtin_amdgcn_readfirstlane(int(it - int64_t(tt) * nk));
+    const int s1 = __builtin_amdgcn_readfirstlane(int(end - it < nk - s0 ? s0 + (end - it) : nk));
+    int tm, tn;
+    group_coords(is_whole ? xcd_remap(b, g.whole) : g.whole + tt, g.tilesM, g.tilesN, &tm, &tn);
+    const int m0 = __builtin_amdgcn_readfirstlane(tm * P::BM), n0 = __builtin_amdgcn_readfirstlane(tn * P::BN);
+    WT w;
+    typename P::COffsets co;
+    co.load(threadIdx.x, g.c, m0, n0, g.M, g.N);
+    P::accumulate(w, ra, rb, g.am + m0, g.ak, g.bk, g.bn + n0, s0, s1, to_lds(smem), co, ctab);
+    if (s1 - s0 == nk) {
+      gett_store_staged<T, T, P::BM, P::BN, P::WGM, P::WGN, false, STREAM>(w, C, ctab, ctab + P::BM, g.M, g.N,
+                                                            g.alpha, g.beta, m0, n0);
+      __syncthreads();   // the C offsets are read before the next piece's are stored
+    } else {
+      constexpr int64_t kSlot = int64_t(WT::FM) * WT::FN * WT::NT;   // 4-vectors per slot
+      gett_store_partial<T, P::BM, P::BN, P::WGM, P::WGN>(
+          w, static_cast<typename WT::acc_t *>(g.ws) + (2 * int64_t(share) + (tt == first ? 0 : 1)) * kSlot);
+    }
+    it += s1 - s0;
+  }
+}
+
+// Adds the pieces of each tile that shares split, in share order, and
+// writes alpha * sum + beta * C.  Workgroup (x, y): tile x of those, and
+// accumulator element y = i * FN + j of every thread.  Tiles that one share
+// covered whole are already written.
+template <typename T, int TILE, bool STREAM>
+__global__ __launch_bounds__(64 * packed_tile<T>(TILE).wgm * packed_tile<T>(TILE).wgn) void packed_fixup_kernel(
+    PackedLaunch g) {
+  typedef PackedKernel<T, TILE, 0, 0> P;
+  typedef typename P::WT WT;
+  typedef typename WT::acc_t acc_t;
+  const int nk = (g.K + P::BK - 1) / P::BK;
+  const int tt = blockIdx.x, f = blockIdx.y;
+  const int64_t I = int64_t(g.tilesM * g.tilesN - g.whole) * nk;
+  // the shares holding the tile's first and last step: the largest s with
+  // share_begin(s) <= x is floor(((x + 1) * S - 1) / I)
+  const int64_t x0 = int64_t(tt) * nk, x1 = x0 + nk - 1;
+  const int lo = int(((x0 + 1) * g.shares - 1) / I), hi = int(((x1 + 1) * g.shares - 1) / I);
+  if (lo == hi) return;
+  constexpr int64_t kSlot = int64_t(WT::FM) * WT::FN * WT::NT;
+  const glb_t<const acc_t> *const ws = to_glb(static_cast<const acc_t *>(g.ws)) + int64_t(f) * WT::NT + threadIdx.x;
+  // only the first share may have begun in an earlier tile
+  acc_t v = ws[(2 * int64_t(lo) + (share_begin(I, g.shares, lo) >= x0 ? 0 : 1)) * kSlot];
+  for (int s = lo + 1; s <= hi; ++s) v = v + ws[2 * int64_t(s) * kSlot];
+  int tm, tn;
+  group_coords(g.whole + tt, g.tilesM, g.tilesN, &tm, &tn);
+  gett_store_fragment<T, T, P::BM, P::BN, P::WGM, P::WGN, STREAM>(v, f / WT::FN, f % WT::FN, static_cast<T *>(g.C),
+                                                                  g.c, g.M, g.N, g.alpha, g.beta,
+                                                                  int64_t(tm) * P::BM, int64_t(tn) * P::BN);
+}
+
+template <typename T, int TILE, int LA, int LB, bool STREAM>
+hipError_t packed_s(const PackedLaunch &g, hipStream_t s) {
+  typedef PackedKernel<T, TILE, LA, LB> P;
+  const int64_t tiles = int64_t((g.M + P::BM - 1) / P::BM) * ((g.N + P::BN - 1) / P::BN);
+  const int64_t nk = (g.K + P::BK - 1) / P::BK;
+  if (g.tilesM != (g.M + P::BM - 1) / P::BM || g.tilesN != (g.N + P::BN - 1) / P::BN || g.whole < 0 ||
+      g.whole > tiles || g.shares < 0 || (g.shares == 0) != (g.whole == tiles) ||
+      int64_t(g.shares) > (tiles - g.whole) * nk || int64_t(g.whole) + g.shares > INT32_MAX || (g.shares && !g.ws) ||
+      (int64_t(g.whole) + g.shares) * P::NT > int64_t(UINT32_MAX) || (g.xa && (g.shares || !g.xb || !g.xc)))
+    return hipErrorInvalidValue;
+  if (g.xa) {
+    constexpr int64_t kMaxY = 65535;   // grid limit along y
+    for (int64_t e0 = 0; e0 < g.entries; e0 += kMaxY) {
+      PackedLaunch q = g;
+      q.first = e0;
+      hipLaunchKernelGGL((packed_kernel<T, TILE, LA, LB, STREAM>),
+                         dim3(unsigned(g.whole), unsigned(g.entries - e0 < kMaxY ? g.entries - e0 : kMaxY)),
+                         dim3(P::NT), 0, s, q);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  hipLaunchKernelGGL((packed_kernel<T, TILE, LA, LB, STREAM>), dim3(unsigned(g.whole + g.shares)), dim3(P::NT), 0, s,
+                     g);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || g.shares == 0) return e;
+  hipLaunchKernelGGL((packed_fixup_kernel<T, TILE, STREAM>), dim3(unsigned(tiles - g.whole), P::WT::FM * P::WT::FN),
+                     dim3(P::NT), 0, s, g);
+  return hipGetLastError();
+}
+
+template <typename T, int TILE, int LA, int LB>
+hipError_t packed_l(const PackedLaunch &g, int *occupancy, hipStream_t s) {
+  if (occupancy)
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(occupancy, packed_kernel<T, TILE, LA, LB, true>,
+                                                        PackedKernel<T, TILE, LA, LB>::NT, 0);
+  // C past the caches only where every store writes whole 64-byte segments.
+  // Whole segments: streaming is faster (K = 32, FP64, 8192 x 16384 with
+  // C in runs of 16: 266 us against 309).  Parts of one: the neighbours'
+  // stores have to meet in the cache (K = 31, 6975 x 14415, runs of 15: 530
+  // us streamed, 219 us plain; FP32 549 and 154 us).
+  const bool stream = g.c_segments && reinterpret_cast<uintptr_t>(g.C) % 64 == 0;
+  return stream ? packed_s<T, TILE, LA, LB, true>(g, s) : packed_s<T, TILE, LA, LB, false>(g, s);
+}
+
+template <typename T, int TILE>
+hipError_t packed_t(const PackedLaunch &g, int *occupancy, hipStream_t s) {
+  switch (g.layoutA * 2 + g.layoutB) {
+    case 0: return packed_l<T, TILE, 0, 0>(g, occupancy, s);
+    case 1: return packed_l<T, TILE, 0, 1>(g, occupancy, s);
+    case 2: return packed_l<T, TILE, 1, 0>(g, occupancy, s);
+    default: return packed_l<T, TILE, 1, 1>(g, occupancy, s);
+  }
+}
+
+template <typename T>
+hipError_t packed_d(const PackedLaunch &g, int *occupancy, hipStream_t s) {
+  switch (g.tile) {
+    case 0: return packed_t<T, 0>(g, occupancy, s);
+    case 1: return packed_t<T, 1>(g, occupancy, s);
+    case 2: return packed_t<T, 2>(g, occupancy, s);
+    case 3: return packed_t<T, 3>(g, occupancy, s);
+    case 4: return packed_t<T, 4>(g, occupancy, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+void packed_tile_shape(int tile, int dtype, int *bm, int *bn, int *bk) {
+  const PackedTile &p = dtype == 0 ? kPacked64[tile] : kPacked32[tile];
+  *bm = p.bm;
+  *bn = p.bn;
+  *bk = p.bk;
+}
+
+hipError_t launch_packed(const PackedLaunch &g, hipStream_t s) {
+  return g.dtype == 0 ? packed_d<double>(g, nullptr, s) : packed_d<float>(g, nullptr, s);
+}
+
+int packed_occupancy(int tile, int dtype, int layoutA, int layoutB) {
+  static std::mutex mu;
+  static std::map<std::array<int, 5>, int> known;   // it depends on the kernel alone
+  int device = 0;
+  (void)hipGetDevice(&device);
+  const std::array<int, 5> key = {device, tile, dtype, layoutA, layoutB};
+  std::lock_guard<std::mutex> lk(mu);
+  const auto it = known.find(key);
+  if (it != known.end()) return it->second;
+  PackedLaunch g{};
+  g.tile = tile;
+  g.dtype = dtype;
+  g.layoutA = layoutA;
+  g.layoutB = layoutB;
+  int n = 0;
+  const hipError_t e = dtype == 0 ? packed_d<double>(g, &n, nullptr) : packed_d<float>(g, &n, nullptr);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    n = 0;
+  }
+  known[key] = n;
+  return n;
+}
+
+}  // namespace comet

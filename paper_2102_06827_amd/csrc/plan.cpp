@@ -115,6 +115,12 @@ static Status strides_for(const std::string &labs, const std::vector<int64_t> &e
   return Status{};
 }
 
+double unit_steps(const std::vector<int64_t> &off) {
+  size_t n = 0;
+  for (size_t t = 1; t < off.size(); ++t) n += off[t] == off[t - 1] + 1;
+  return off.size() > 1 ? double(n) / double(off.size() - 1) : 0.0;
+}
+
 int contiguous_run(const std::vector<int64_t> &off) {
   const int64_t n = (int64_t)off.size();
   for (int v = 8; v > 1; v /= 2) {
@@ -605,8 +611,14 @@ Status analyze(const char *spec, const int64_t *extents, const int64_t *strides_
       an.runAk = contiguous_run(an.offAk);
       an.runBk = contiguous_run(an.offBk);
     }
-    an.layoutA = an.runAm > an.runAk ? LAYOUT_MN_CONTIG : LAYOUT_K_CONTIG;
-    an.layoutB = an.runBn > an.runBk ? LAYOUT_MN_CONTIG : LAYOUT_K_CONTIG;
+    // the longer run; where neither index has one of at least two (an odd
+    // extent breaks them), the index with more unit steps
+    auto layout = [&](const std::vector<int64_t> &r, int run_r, const std::vector<int64_t> &k, int run_k) {
+      const bool along_r = run_r == 1 && run_k == 1 && !an.empty_sum ? unit_steps(r) > unit_steps(k) : run_r > run_k;
+      return along_r ? LAYOUT_MN_CONTIG : LAYOUT_K_CONTIG;
+    };
+    an.layoutA = layout(an.offAm, an.runAm, an.offAk, an.runAk);
+    an.layoutB = layout(an.offBn, an.runBn, an.offBk, an.runBk);
     auto maxv = [](const std::vector<int64_t> &v) { return v.empty() ? 0 : *std::max_element(v.begin(), v.end()); };
     const int64_t lim = int64_t(1) << 31;
     an.tables32 = maxv(an.offAm) + maxv(an.offAk) < lim && maxv(an.offBk) + maxv(an.offBn) < lim &&
@@ -661,7 +673,8 @@ std::string describe_json(const Analysis &an) {
   o << ",\"layoutB\":\"" << (an.layoutB == LAYOUT_K_CONTIG ? "k" : "n") << "\"";
   o << ",\"tables32\":" << (an.tables32 ? "true" : "false");
   o << ",\"tile\":" << an.tile << ",\"sk_tiles\":" << an.sk_tiles << ",\"sk_blocks\":" << an.sk_blocks << ",\"even\":" << an.even << ",\"even_whole\":" << an.even_whole << ",\"persist\":" << an.persist
-    << ",\"shortk\":" << an.shortk << ",\"gemv\":" << an.gemv << ",\"gemv_split\":" << an.gemv_split;
+    << ",\"shortk\":" << an.shortk << ",\"gemv\":" << an.gemv << ",\"gemv_split\":" << an.gemv_split
+    << ",\"packed\":" << an.packed << ",\"packed_whole\":" << an.packed_whole << ",\"packed_shares\":" << an.packed_shares;
   o << ",\"split_slices\":" << an.split_slices;
   o << ",\"empty_out\":" << (an.empty_out ? "true" : "false") << ",\"empty_sum\":" << (an.empty_sum ? "true" : "false");
   if (an.path == COMET_PATH_TTGT) {

@@ -108,6 +108,10 @@ struct Analysis {
   int gemv = 0;
   int gemv_split = 0;
   int64_t gemv_slab = 0;
+  // > 0: the packed gather kernel (single-element loads, any strides) with
+  // its tile packed - 1: packed_whole tiles computed whole, the others shared
+  // by packed_shares workgroups
+  int packed = 0, packed_whole = 0, packed_shares = 0;
   int split_slices = 5;
 
   TTGTChoice ttgt;
@@ -155,6 +159,8 @@ PermuteDesc make_permute(const std::string &out_labels, const std::vector<int64_
 // Largest v in {8,4,2,1} such that the table is made of runs off[t..t+v) =
 // off[t] + 0..v-1 starting at every multiple of v, and v divides its length.
 int contiguous_run(const std::vector<int64_t> &off);
+// The share of a table's steps that are 1.
+double unit_steps(const std::vector<int64_t> &off);
 
 std::string describe_json(const Analysis &an);
 

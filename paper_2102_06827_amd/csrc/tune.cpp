@@ -2,7 +2,7 @@
 //
 // File format (one object; unknown or malformed content makes the whole file
 // ignored and rewritten):
-//   {"format": "comet-tune-2", "entries": {"<key>": {"tile": 3, "path": 1, "us": 1234.5, "ttgt": ""}, ...}}
+//   {"format": "comet-tune-2", "entries": {"<key>": {"tile": 3, "path": 1, "us": 1234.5, "packed": 0, "ttgt": ""}, ...}}
 #include "tune.hpp"
 
 #include <cmath>
@@ -17,7 +17,7 @@ namespace comet {
 
 namespace {
 const char *kFormat = "comet-tune-2";
-const char *kKernelVersion = "k11";   // bump when kernels change in a way that invalidates timings
+const char *kKernelVersion = "k12";   // bump when kernels change in a way that invalidates timings
 
 int bucket(int64_t x) {
   int b = 0;
@@ -60,6 +60,8 @@ bool parse(const std::string &text, std::map<std::string, TuneEntry> &out) {
     e.tile = tile;
     e.path = path;
     e.us = us;
+    const size_t pq = body.find("\"packed\": ");
+    if (pq != std::string::npos) e.packed = std::atoi(body.c_str() + pq + 10);
     const size_t tq = body.find("\"ttgt\": \"");
     if (tq != std::string::npos) {
       const size_t t0 = tq + 9, t1 = body.find('"', t0);
@@ -117,8 +119,8 @@ void TuneCache::save() const {
     bool first = true;
     char buf[256];
     for (const auto &kv : entries_) {
-      std::snprintf(buf, sizeof buf, "{\"tile\": %d, \"path\": %d, \"us\": %.3f, \"ttgt\": \"%s\"}", kv.second.tile,
-                    kv.second.path, kv.second.us, kv.second.ttgt.c_str());
+      std::snprintf(buf, sizeof buf, "{\"tile\": %d, \"path\": %d, \"us\": %.3f, \"packed\": %d, \"ttgt\": \"%s\"}", kv.second.tile,
+                    kv.second.path, kv.second.us, kv.second.packed, kv.second.ttgt.c_str());
       f << (first ? "\n" : ",\n") << "  \"" << kv.first << "\": " << buf;
       first = false;
     }

@@ -16,6 +16,9 @@ struct TuneEntry {
   int path = COMET_PATH_GETT;
   double us = 0.0;
   std::string ttgt;   // for path TTGT: "A order|B order|C order" of the fastest flattening
+  // nonzero: the packed gather kernel, by its own schedule (tile is then the
+  // gather tile it stands in for)
+  int packed = 0;
 };
 
 class TuneCache {
