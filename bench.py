@@ -874,7 +874,8 @@ def main():
     Ad = torch.empty(shape("acik"), dtype=torch.float64, device="cuda")
     Bd = torch.empty(shape("bkcj"), dtype=torch.float64, device="cuda")
     sched = comet.Plan(SPEC, Ad, Bd, compute="f64").describe()
-    sched = {k: sched[k] for k in ("path", "tile", "sk_tiles", "sk_blocks", "even", "even_whole", "resident")}
+    sched = {k: sched[k] for k in ("path", "tile", "sk_tiles", "sk_blocks", "even", "even_whole", "resident", "packed",
+                                "packed_whole", "packed_shares")}
     del Ad, Bd
     same = (HEADLINE_TRAFFIC["kernel_version"] == KERNEL_VERSION and
             all(HEADLINE_TRAFFIC["schedule"][k] == sched[k] for k in HEADLINE_TRAFFIC["schedule"]))

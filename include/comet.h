@@ -272,9 +272,11 @@ comet_status_t comet_analyze(const char *spec, const int64_t *extents,
 
 /*
  * Batch API: n independent contractions in ONE persistent kernel launch.
+ * Native products run on the packed gather kernel's tiles (single-element
+ * loads: any strides and extents) unless a problem's operand reaches 2 GiB
+ * (then, and with COMET_PACKED=0, the whole batch on the vector-load tiles).
  * Every problem gets a tile class (64 x 64, 128 x 64, 64 x 128 or 128 x 128
- * outputs per workgroup; element-load problems and FP64 use the classes
- * their kernels have): COMET_BATCH_CLASS=<class> forces one, the autotuner
+ * outputs per workgroup, those that the batch's kernel has): COMET_BATCH_CLASS=<class> forces one, the autotuner
  * (comet_autotune on) times the classes per problem class (storage dtype,
  * compute, operand layouts, power-of-two buckets of the flattened sizes) on
  * a batch of copies of a representative problem and caches the winner, and
@@ -284,11 +286,10 @@ comet_status_t comet_analyze(const char *spec, const int64_t *extents,
  * tile rows.  Workgroups take (problem, tile) items from their XCD's queue
  * through a device counter and move on to the other queues once it is
  * drained, so many small, uneven problems fill the GPU together.  A problem
- * whose operands only the element-load kernel could gather (their unit
- * strides on different summation labels) gets a dense copy of one operand,
- * held by the batch and refreshed by every execute before the launch, in a
- * label order both operands can be read from in 16-byte vectors
- * (COMET_BATCH_COPY=0 keeps the element-load kernel instead).
+ * whose operands have their unit strides on different summation labels gets
+ * a dense copy of one operand, held by the batch and refreshed by every
+ * execute before the launch (all copies in one launch), in a label order both
+ * operands can be read from in runs (COMET_BATCH_COPY=0 reads it in place).
  * All problems share dtype and compute; compute must be the storage type's
  * native MFMA (DEFAULT, or F64 / F32 matching the dtype), or SPLIT_BF16X3
  * with FP32 storage (operands split into three bfloat16 slices inside the

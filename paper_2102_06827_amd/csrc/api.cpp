@@ -124,6 +124,10 @@ struct comet_batch_s {
   // element-load problems: one operand copied, before the launch, into a
   // dense order that both operands can read in vectors (pbuf, owned here)
   void *pbuf = nullptr;
+  int ncopies = 0;                 // copies in all: one launch for the transposes, one each for the rest
+  const void *copies = nullptr;    // (in dbuf)
+  int ntiled = 0;
+  int64_t copy_blocks = 0;
   std::vector<PermuteLaunch> perms;
 
   ~comet_batch_s() {
@@ -143,6 +147,18 @@ bool packed_can(const Analysis &an) {
   const int64_t sizes = int64_t(INT32_MAX) - 1024;
   return native && !an.empty_out && !an.empty_sum && an.sizeA < lim && an.sizeB < lim &&
          an.m < sizes && an.n < sizes && an.k < sizes;
+}
+
+// A packed kernel's table in bytes: offsets in 32 bits, rows padded to a
+// whole tile with the last one, summation indices with kPackedOut, whose loads
+// give zeros.
+size_t packed_table_len(const std::vector<int64_t> &t, bool rows) {
+  return rows ? (t.size() + kPackedRowPad - 1) / kPackedRowPad * kPackedRowPad : t.size() + kPackedKPad;
+}
+void packed_table(const std::vector<int64_t> &t, bool rows, size_t es, uint32_t *out) {
+  const size_t n = t.size(), len = packed_table_len(t, rows);
+  for (size_t j = 0; j < n; ++j) out[j] = uint32_t(t[j] * int64_t(es));
+  for (size_t j = n; j < len; ++j) out[j] = rows ? out[n - 1] : kPackedOut;
 }
 
 // Whether C's offsets come in whole 64-byte segments along n, aligned to 64
@@ -168,28 +184,19 @@ comet_status_t upload_tables(comet_plan_s *p) {
     off[i] = total;
     total += align256(std::max<size_t>(tabs[i]->size(), 1) * sizeof(int64_t));
   }
-  // the packed kernel's tables: byte offsets in 32 bits, the last entry
-  // repeated over the padding
   const bool packed = packed_can(an);
   const size_t es = elem_size(an.dtype);
-  size_t poff[4] = {0, 0, 0, 0}, plen[4] = {0, 0, 0, 0};
+  size_t poff[4] = {0, 0, 0, 0};
   for (int i = 0; packed && i < 4; ++i) {
-    const size_t n = tabs[i]->size();
-    plen[i] = i == 0 || i == 3 ? (n + kPackedRowPad - 1) / kPackedRowPad * kPackedRowPad : n + kPackedKPad;
     poff[i] = total;
-    total += align256(plen[i] * sizeof(uint32_t));
+    total += align256(packed_table_len(*tabs[i], i == 0 || i == 3) * sizeof(uint32_t));
   }
   HIP_TRY(hipMalloc(&p->dtables, total), "hipMalloc(offset tables)");
   std::vector<char> host(total, 0);
   for (int i = 0; i < 9; ++i)
     if (!tabs[i]->empty()) std::memcpy(host.data() + off[i], tabs[i]->data(), tabs[i]->size() * sizeof(int64_t));
-  for (int i = 0; packed && i < 4; ++i) {
-    uint32_t *t = reinterpret_cast<uint32_t *>(host.data() + poff[i]);
-    const size_t n = tabs[i]->size();
-    const bool rows = i == 0 || i == 3;
-    for (size_t j = 0; j < plen[i]; ++j)
-      t[j] = j >= n && !rows ? kPackedOut : uint32_t((*tabs[i])[std::min(j, n - 1)] * int64_t(es));
-  }
+  for (int i = 0; packed && i < 4; ++i)
+    packed_table(*tabs[i], i == 0 || i == 3, es, reinterpret_cast<uint32_t *>(host.data() + poff[i]));
   HIP_TRY(hipMemcpy(p->dtables, host.data(), total, hipMemcpyHostToDevice), "hipMemcpy(offset tables)");
   char *b = static_cast<char *>(p->dtables);
   p->t.offAm = reinterpret_cast<const int64_t *>(b + off[0]);
@@ -276,10 +283,9 @@ constexpr double kSkLaunchUs = 4.0;      // the two extra launches
 // in runs of at least two elements on average: its loads are then as good as
 // those of TTGT's matrices (1725^3 in FP64, extents of 75 and 23: 286 us by
 // TTGT's permutes and its element-load GEMM, 175 us read in place).
-bool packed_reads(const comet_plan_s *p) {
-  const Analysis &an = p->an;
+bool packed_reads(const Analysis &an) {
   const char *env = std::getenv("COMET_PACKED");
-  if (!p->pk.am || (env && std::strcmp(env, "0") == 0)) return false;
+  if (!packed_can(an) || (env && std::strcmp(env, "0") == 0)) return false;
   return unit_steps(an.layoutA == LAYOUT_MN_CONTIG ? an.offAm : an.offAk) >= 0.5 &&
          unit_steps(an.layoutB == LAYOUT_MN_CONTIG ? an.offBn : an.offBk) >= 0.5;
 }
@@ -915,7 +921,7 @@ comet_status_t build_plan(std::unique_ptr<comet_plan_s> &out, const char *spec, 
                              std::getenv("COMET_GETT_PERSIST") || std::getenv("COMET_GETT_EVEN");
   if (path == COMET_PATH_AUTO && native && !tuning && !gather_forced && an.path == COMET_PATH_GETT &&
       an.X.empty() && !an.empty_out && !an.empty_sum && !(p->vecA_tables && p->vecB_tables) &&
-      !packed_reads(p.get())) {
+      !packed_reads(an)) {
     std::unique_ptr<comet_plan_s> tt;
     if (build_plan(tt, spec, extents, sA, sB, sC, dtype, compute, COMET_PATH_TTGT, false) == COMET_OK && tt->gemm &&
         tt->ws_bytes <= kTTGTMaxWorkspace && ttgt_saving_s(an, *tt) > 0.0) {
@@ -1523,6 +1529,8 @@ comet_status_t autotune_plan(std::unique_ptr<comet_plan_s> &p, const char *spec,
 // the summation labels in the order of the other operand's strides (so both
 // share the unit-stride summation label), or the summation labels first.
 // The copy's analysis replaces the problem's; `which` is 0 for A, 1 for B.
+// packed: for the packed kernel, which reads short runs as well as long ones:
+// an order in which both operands have runs of at least two on average.
 struct BatchCopy {
   int which = -1;
   std::string order;            // labels of the copy, outermost first
@@ -1531,7 +1539,7 @@ struct BatchCopy {
 };
 
 bool batch_copy_choice(const comet_problem_t &pr, const Analysis &a, comet_dtype_t dtype, comet_compute_t compute,
-                       int VEC, Analysis &out, BatchCopy &cp) {
+                       int VEC, bool packed, Analysis &out, BatchCopy &cp) {
   if (!a.X.empty() || a.empty_out || a.empty_sum) return false;
   const std::string &la = a.spec_a, &lb = a.spec_b, &lc = a.spec_c;
   auto ext_of = [&](char ch) {
@@ -1576,8 +1584,9 @@ bool batch_copy_choice(const comet_problem_t &pr, const Analysis &a, comet_dtype
                                 which == 1 ? sxn.data() : sb.data(), sc.data(), dtype, compute, COMET_PATH_GETT,
                                 g_split_slices, na, g_int8_slices);
       if (!st.ok()) continue;
-      if (tables_vec_ok(na.offAm, na.offAk, na.layoutA, na.runAm, na.runAk, VEC) &&
-          tables_vec_ok(na.offBn, na.offBk, na.layoutB, na.runBn, na.runBk, VEC)) {
+      if (packed ? packed_reads(na)
+                 : tables_vec_ok(na.offAm, na.offAk, na.layoutA, na.runAm, na.runAk, VEC) &&
+                       tables_vec_ok(na.offBn, na.offBk, na.layoutB, na.runBn, na.runBk, VEC)) {
         out = na;
         cp.which = which;
         cp.order = order;
@@ -1590,6 +1599,15 @@ bool batch_copy_choice(const comet_problem_t &pr, const Analysis &a, comet_dtype
   return false;
 }
 
+// The 64-bit tables a batch uploads for a problem, by their place in GettTables
+// (C's batch table last): the packed kernel has the operands' in 32 bits.
+std::vector<const std::vector<int64_t> *> batch_tables(const Analysis &a, bool packed) {
+  static const std::vector<int64_t> none;
+  const std::vector<int64_t> *z = &none;
+  return {packed ? z : &a.offAm, packed ? z : &a.offAk, packed ? z : &a.offBk, packed ? z : &a.offBn,
+          &a.offCm, &a.offCn, &a.offCx};
+}
+
 // ---- batch tile classes -------------------------------------------------------
 
 // Output elements per unit time of each batch tile class relative to the
@@ -1597,23 +1615,30 @@ bool batch_copy_choice(const comet_problem_t &pr, const Analysis &a, comet_dtype
 // choice; the autotuner replaces it with timings).
 constexpr double kBatchRateNative[kBatchClasses] = {1.0, 1.12, 1.12, 1.25};
 constexpr double kBatchRateFused[kBatchClasses] = {1.0, 1.3, 1.3, 1.7};
+constexpr double kBatchRatePacked[2][kBatchClasses] = {{1.0, 1.05, 1.05, 1.0}, {1.0, 1.08, 1.08, 1.14}};
 
 // Modeled time of a descriptor in class `cls`: its padded output area times
 // its summation length over the class's rate.
-double batch_class_cost(const BatchDesc &d, int cls, int mode) {
+double batch_class_cost(const BatchDesc &d, int cls, int dt, int mode) {
   int bm, bn;
   batch_class_shape(cls, &bm, &bn);
   const double area = double((d.M + bm - 1) / bm) * bm * double((d.N + bn - 1) / bn) * bn;
-  return area * double(d.K) / (mode == 1 ? kBatchRateFused[cls] : kBatchRateNative[cls]);
+  return area * double(d.K) / (mode == 2   ? kBatchRatePacked[dt][cls]
+                               : mode == 1 ? kBatchRateFused[cls]
+                                           : kBatchRateNative[cls]);
 }
 
-int batch_model_class(const BatchDesc &d, int dt, int mode) {
+// max_area: no class of more outputs than this (class 0 always)
+int batch_model_class(const BatchDesc &d, int dt, int mode, int max_area = INT_MAX) {
   const bool vec = d.variant < 4;
   int best = 0;
-  double bc = batch_class_cost(d, 0, mode);
+  double bc = batch_class_cost(d, 0, dt, mode);
   for (int c = 1; c < kBatchClasses; ++c) {
     if (!batch_class_valid(c, dt, mode, vec)) continue;
-    const double x = batch_class_cost(d, c, mode);
+    int bm, bn;
+    batch_class_shape(c, &bm, &bn);
+    if (bm * bn > max_area) continue;
+    const double x = batch_class_cost(d, c, dt, mode);
     if (x < bc * 0.999) {
       best = c;
       bc = x;
@@ -1633,13 +1658,44 @@ comet_status_t batch_choose_classes(const std::vector<Analysis> &an, const std::
                                     int mode) {
   const char *env = std::getenv("COMET_BATCH_CLASS");
   const int forced = (env && *env) ? std::atoi(env) : -1;
+  // The packed kernel's classes run at nearly one rate, so in a batch that
+  // fills the chip only a few times over the last items to finish decide:
+  // the largest class allowed is the one with the least work per workgroup
+  // plus a quarter of its longest item (48 contractions with extents of up to
+  // 33, FP32: 192 us with 128 x 128 tiles, 151 with half of them).
+  int max_area = INT_MAX;
+  if (mode == 2 && forced < 0) {
+    int device = 0, cus = 256;
+    if (hipGetDevice(&device) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
+      cus = 256;
+    const double slots = double(cus) * batch_blocks_per_cu(dt, mode);
+    double best = 1e300;
+    for (const int area : {128 * 128, 128 * 64, 64 * 64}) {
+      double total = 0.0, longest = 0.0;
+      for (size_t j = 0; j < descs.size(); ++j) {
+        if (!live[j]) continue;
+        const BatchDesc &d = descs[j];
+        const int c = batch_model_class(d, dt, mode, area);
+        int bm, bn;
+        batch_class_shape(c, &bm, &bn);
+        const double cost = batch_class_cost(d, c, dt, mode);
+        total += cost;
+        longest = std::max(longest, cost / (double((d.M + bm - 1) / bm) * double((d.N + bn - 1) / bn)));
+      }
+      if (total / slots + 0.25 * longest < best) {
+        best = total / slots + 0.25 * longest;
+        max_area = area;
+      }
+    }
+  }
   for (size_t j = 0; j < descs.size(); ++j) {
     BatchDesc &d = descs[j];
     if (!live[j]) continue;
     if (forced >= 0)
       d.cls = batch_class_valid(forced, dt, mode, d.variant < 4) ? forced : 0;
     else
-      d.cls = batch_model_class(d, dt, mode);
+      d.cls = batch_model_class(d, dt, mode, max_area);
   }
   if (forced < 0 && tune_cache().mode() != 0) return batch_tune_classes(an, first, live, descs, dt, mode);
   return COMET_OK;
@@ -1707,6 +1763,11 @@ comet_status_t batch_tune_classes(const std::vector<Analysis> &an, const std::ve
       offs[t] = tb;
       tb += align256(std::max<size_t>(tabs[t]->size(), 1) * sizeof(int64_t));
     }
+    size_t poffs[4] = {0, 0, 0, 0};
+    for (int t = 0; mode == 2 && t < 4; ++t) {
+      poffs[t] = tb;
+      tb += align256(packed_table_len(*tabs[t], t == 0 || t == 3) * sizeof(uint32_t));
+    }
     const int64_t nA = std::max<int64_t>(a.swapped ? a.sizeB : a.sizeA, 1);
     const int64_t nB = std::max<int64_t>(a.swapped ? a.sizeA : a.sizeB, 1);
     const int64_t nC = std::max<int64_t>(a.sizeC, 1);
@@ -1731,6 +1792,8 @@ comet_status_t batch_tune_classes(const std::vector<Analysis> &an, const std::ve
       std::vector<char> host(oA, 0);
       for (int t = 0; t < 6; ++t)
         if (!tabs[t]->empty()) std::memcpy(host.data() + offs[t], tabs[t]->data(), tabs[t]->size() * sizeof(int64_t));
+      for (int t = 0; mode == 2 && t < 4; ++t)
+        packed_table(*tabs[t], t == 0 || t == 3, es, reinterpret_cast<uint32_t *>(host.data() + poffs[t]));
       ok = hipMemcpy(b, host.data(), oA, hipMemcpyHostToDevice) == hipSuccess &&
            fill_value(b + oA, nA, dt, 0.5, s) == hipSuccess && fill_value(b + oB, nB, dt, -0.25, s) == hipSuccess;
       BatchDesc td = d;
@@ -1741,6 +1804,15 @@ comet_status_t batch_tune_classes(const std::vector<Analysis> &an, const std::ve
       td.beta = 0.0;
       auto T = [&](int t) { return reinterpret_cast<const int64_t *>(b + offs[t]); };
       td.t = GettTables{T(0), T(1), T(2), T(3), T(4), T(5)};
+      if (mode == 2) {
+        auto P = [&](int t) { return reinterpret_cast<const uint32_t *>(b + poffs[t]); };
+        td.am = P(0);
+        td.ak = P(1);
+        td.bk = P(2);
+        td.bn = P(3);
+        td.bytesA = uint32_t(nA * int64_t(es));
+        td.bytesB = uint32_t(nB * int64_t(es));
+      }
       for (int c = 0; ok && c < kBatchClasses; ++c) {
         if (!batch_class_valid(c, dt, mode, d.variant < 4)) continue;
         int bm, bn;
@@ -2246,6 +2318,15 @@ comet_status_t comet_batch_create(comet_batch_t *batch, int n, const comet_probl
     if (reads && (pr.C == pr.A || pr.C == pr.B))
       return fail(COMET_ERR_UNSUPPORTED, "problem " + std::to_string(i) + ": C aliases an input");
   }
+  // the packed kernel, where it can run every problem (COMET_PACKED=0: the
+  // vector-load one)
+  bool packed = b->mode == 0;
+  if (const char *env = std::getenv("COMET_PACKED"); env && std::strcmp(env, "0") == 0) packed = false;
+  for (int i = 0; packed && i < n; ++i) {
+    const Analysis &a = an[i];
+    if (!a.empty_out && !a.empty_sum && problems[i].alpha != 0.0 && !packed_can(a)) packed = false;
+  }
+  if (packed) b->mode = 2;
   // dense copies of one operand of each element-load problem (COMET_BATCH_COPY=0
   // keeps the element-load kernel for them)
   const int VEC = dtype == COMET_F64 ? 2 : 4;
@@ -2259,11 +2340,12 @@ comet_status_t comet_batch_create(comet_batch_t *batch, int n, const comet_probl
       const Analysis &a = an[i];
       const comet_problem_t &pr = problems[i];
       if (a.empty_out || a.empty_sum || pr.alpha == 0.0) continue;
-      if (tables_vec_ok(a.offAm, a.offAk, a.layoutA, a.runAm, a.runAk, VEC) &&
-          tables_vec_ok(a.offBn, a.offBk, a.layoutB, a.runBn, a.runBk, VEC))
+      if (packed ? packed_reads(a)
+                 : tables_vec_ok(a.offAm, a.offAk, a.layoutA, a.runAm, a.runAk, VEC) &&
+                       tables_vec_ok(a.offBn, a.offBk, a.layoutB, a.runBn, a.runBk, VEC))
         continue;
       Analysis na;
-      if (batch_copy_choice(pr, a, dtype, compute, VEC, na, copies[i])) {
+      if (batch_copy_choice(pr, a, dtype, compute, VEC, packed, na, copies[i])) {
         an[i] = na;
         copy_off[i] = copy_bytes;
         copy_bytes += align256(size_t(copies[i].count) * elem_size(dtype));
@@ -2290,8 +2372,11 @@ comet_status_t comet_batch_create(comet_batch_t *batch, int n, const comet_probl
   for (int i = 0; i < n; ++i) {
     tab_off[i] = bytes;
     const Analysis &a = an[i];
-    for (const std::vector<int64_t> *v : {&a.offAm, &a.offAk, &a.offBk, &a.offBn, &a.offCm, &a.offCn, &a.offCx})
+    for (const std::vector<int64_t> *v : batch_tables(a, packed))
       bytes += align256(std::max<size_t>(v->size(), 1) * sizeof(int64_t));
+    const std::vector<int64_t> *pt[4] = {&a.offAm, &a.offAk, &a.offBk, &a.offBn};
+    for (int t = 0; packed && t < 4 && live[size_t(first[i])]; ++t)
+      bytes += align256(packed_table_len(*pt[t], t == 0 || t == 3) * sizeof(uint32_t));
   }
   const size_t es = elem_size(dtype);
   const int dt = dtype == COMET_F64 ? 0 : 1;
@@ -2349,8 +2434,11 @@ comet_status_t comet_batch_create(comet_batch_t *batch, int n, const comet_probl
     return fail(COMET_ERR_UNSUPPORTED, "batch has more than 2^31 - 2^20 output tiles");
   const size_t items_off = bytes;
   bytes += align256(sizeof(BatchItem) * std::max<int64_t>(total, 1));
+  const size_t copies_off = bytes;
+  for (const BatchCopy &cp : copies) bytes += cp.which >= 0 ? permute_copy_stride() : 0;
+  bytes = align256(bytes);
+  std::vector<char> copy_entries;
   HIP_TRY(hipGetDevice(&b->device), "hipGetDevice");
-  HIP_TRY(hipMalloc(&b->dbuf, bytes), "hipMalloc(batch)");
   if (copy_bytes > 0) {
     HIP_TRY(hipMalloc(&b->pbuf, copy_bytes), "hipMalloc(batch copies)");
     for (int i = 0; i < n; ++i) {
@@ -2384,10 +2472,27 @@ comet_status_t comet_batch_create(comet_batch_t *batch, int n, const comet_probl
       pl.alpha = 1.0;
       pl.beta = 0.0;
       pl.dtype = dtype == COMET_F64 ? 0 : 1;
-      b->perms.push_back(pl);
+      // into the one launch of the transposes, while its grid has room (2^22
+      // workgroups)
+      b->ncopies += 1;
+      const size_t at = copy_entries.size();
+      copy_entries.resize(at + permute_copy_stride());
+      const int64_t blocks = permute_copy_entry(pl, b->copy_blocks, copy_entries.data() + at);
+      if (blocks > 0 && b->copy_blocks + blocks <= (int64_t(1) << 22)) {
+        b->copy_blocks += blocks;
+        b->ntiled += 1;
+      } else {
+        copy_entries.resize(at);
+        b->perms.push_back(pl);
+      }
     }
   }
+  HIP_TRY(hipMalloc(&b->dbuf, bytes), "hipMalloc(batch)");
   std::vector<char> host(bytes, 0);
+  if (!copy_entries.empty()) {
+    std::memcpy(host.data() + copies_off, copy_entries.data(), copy_entries.size());
+    b->copies = static_cast<char *>(b->dbuf) + copies_off;
+  }
   char *dev = static_cast<char *>(b->dbuf);
   for (int i = 0; i < n; ++i) {
     const Analysis &a = an[i];
@@ -2395,13 +2500,30 @@ comet_status_t comet_batch_create(comet_batch_t *batch, int n, const comet_probl
     size_t off = tab_off[i];
     const int64_t *ptr[7];
     int k = 0;
-    for (const std::vector<int64_t> *v : {&a.offAm, &a.offAk, &a.offBk, &a.offBn, &a.offCm, &a.offCn, &a.offCx}) {
+    for (const std::vector<int64_t> *v : batch_tables(a, packed)) {
       if (!v->empty()) std::memcpy(host.data() + off, v->data(), v->size() * sizeof(int64_t));
       ptr[k++] = reinterpret_cast<const int64_t *>(dev + off);
       off += align256(std::max<size_t>(v->size(), 1) * sizeof(int64_t));
     }
-    for (int64_t e = 0; e < (a.empty_out ? 1 : a.nb); ++e)
-      descs[size_t(first[i] + e)].t = GettTables{ptr[0], ptr[1], ptr[2], ptr[3], ptr[4], ptr[5]};
+    const uint32_t *pp[4] = {nullptr, nullptr, nullptr, nullptr};
+    const std::vector<int64_t> *pt[4] = {&a.offAm, &a.offAk, &a.offBk, &a.offBn};
+    for (int t = 0; packed && t < 4 && live[size_t(first[i])]; ++t) {
+      packed_table(*pt[t], t == 0 || t == 3, es, reinterpret_cast<uint32_t *>(host.data() + off));
+      pp[t] = reinterpret_cast<const uint32_t *>(dev + off);
+      off += align256(packed_table_len(*pt[t], t == 0 || t == 3) * sizeof(uint32_t));
+    }
+    for (int64_t e = 0; e < (a.empty_out ? 1 : a.nb); ++e) {
+      BatchDesc &d = descs[size_t(first[i] + e)];
+      d.t = GettTables{ptr[0], ptr[1], ptr[2], ptr[3], ptr[4], ptr[5]};
+      if (!pp[0]) continue;
+      d.am = pp[0];
+      d.ak = pp[1];
+      d.bk = pp[2];
+      d.bn = pp[3];
+      const bool bx = !a.offAx.empty();
+      d.bytesA = uint32_t(((a.swapped ? a.sizeB : a.sizeA) - (bx ? a.offAx[e] : 0)) * int64_t(es));
+      d.bytesB = uint32_t(((a.swapped ? a.sizeA : a.sizeB) - (bx ? a.offBx[e] : 0)) * int64_t(es));
+    }
     if (!a.empty_out && (a.empty_sum || pr.alpha == 0.0)) {
       const double beta = dtype == COMET_F32 ? double(float(pr.beta)) : pr.beta;
       b->scales.push_back({pr.C, ptr[4], ptr[5], a.m, a.n, beta, a.offCx.empty() ? nullptr : ptr[6], a.nb});
@@ -2429,6 +2551,16 @@ comet_status_t comet_batch_create(comet_batch_t *batch, int n, const comet_probl
     qlist[size_t(qmin)].push_back(j);
     load[size_t(qmin)] += cost[size_t(j)];
   }
+  // the longest items first: the last ones to run then end close together
+  for (auto &ql : qlist)
+    std::stable_sort(ql.begin(), ql.end(), [&](int64_t x, int64_t y) {
+      auto item = [&](int64_t j) {
+        int bm, bn;
+        batch_class_shape(descs[size_t(j)].cls, &bm, &bn);
+        return double(bm) * bn * double(descs[size_t(j)].K);
+      };
+      return item(x) > item(y);
+    });
   BatchItem *items = reinterpret_cast<BatchItem *>(host.data() + items_off);
   constexpr int kGroup = 4;
   int64_t w = 0;
@@ -2478,6 +2610,8 @@ comet_status_t comet_batch_execute(comet_batch_t batch, void *workspace, size_t 
     HIP_TRY(launch_scale(sc.C, batch->dtype == COMET_F64 ? 0 : 1, sc.offCm, sc.offCn, sc.m, sc.n, sc.beta, s,
                          sc.offCb, sc.nb),
             "batch scale");
+  HIP_TRY(launch_permute_copies(batch->copies, batch->ntiled, batch->copy_blocks, batch->dtype == COMET_F64 ? 0 : 1, s),
+          "batch operand copies");
   for (const PermuteLaunch &pl : batch->perms) HIP_TRY(launch_permute(pl, s), "batch operand copy");
   HIP_TRY(launch_batch(batch->descs, batch->items, batch->queues, static_cast<int *>(workspace),
                        batch->dtype == COMET_F64 ? 0 : 1, batch->mode, batch->grid, s),
@@ -2493,7 +2627,7 @@ comet_status_t comet_batch_describe(comet_batch_t batch, char *buf, size_t len) 
   js += "],\"queues\":[";
   for (int q = 0; q < kBatchQueues; ++q)
     js += (q ? "," : "") + std::to_string(batch->queues.off[q + 1] - batch->queues.off[q]);
-  js += "],\"tuned\":" + std::to_string(batch->tuned) + ",\"copies\":" + std::to_string(batch->perms.size()) + "}";
+  js += "],\"tuned\":" + std::to_string(batch->tuned) + ",\"copies\":" + std::to_string(batch->ncopies) + "}";
   std::strncpy(buf, js.c_str(), len - 1);
   buf[len - 1] = 0;
   if (js.size() + 1 > len) return fail(COMET_ERR_WORKSPACE, "describe buffer too small");

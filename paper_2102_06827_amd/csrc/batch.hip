@@ -24,8 +24,8 @@
 #include <climits>
 #include <type_traits>
 
-#include "gather.hpp"
 #include "kernels.hpp"
+#include "packed.hpp"
 
 namespace comet {
 namespace {
@@ -269,6 +269,86 @@ __global__ __launch_bounds__(BatchWaves<MODE>::NT, BatchWaves<MODE>::MINB) void 
   }
 }
 
+// The native products on the packed tile product (packed.hpp): element loads
+// in every operand order and alignment, so every problem has the larger
+// classes, in FP64 too (but 128 x 128, which spills there).  Bound by the
+// matrix cores; 4 waves of up to 64 x 64 outputs, two workgroups per CU.
+// MI355X, against the vector-load kernel on the same box (96 problems of up
+// to 64 per extent, forward and both gradients, FP32): 14.07 -> 11.00 ms; 32
+// problems of up to 56, odd extents among them: FP32 4.51 -> 2.46 ms, FP64
+// 5.31 -> 4.23 ms.  128 x 128 tiles run 1.14 times as fast as 64 x 64 in
+// FP32 (128 x 64: 1.08; FP64 1.05).
+constexpr bool packed_class_ok(int cls, int dtype) { return dtype == 1 || cls < 3; }
+template <typename T>
+constexpr int packed_bk() { return sizeof(T) == 8 ? 16 : 32; }
+template <typename T, int CLS, int LA, int LB>
+using BatchCore = packed::PackedCore<T, kClass[CLS].bm, kClass[CLS].bn, packed_bk<T>(), 2, 2, LA, LB>;
+
+template <typename T, int CLS, int LA, int LB>
+__device__ __forceinline__ void packed_item(const BatchDesc &d, int tile, T *smem, int64_t *ctab) {
+  typedef BatchCore<T, CLS, LA, LB> P;
+  const int m0 = __builtin_amdgcn_readfirstlane((tile / d.tilesN) * P::BM);
+  const int n0 = __builtin_amdgcn_readfirstlane((tile % d.tilesN) * P::BN);
+  const int K = int(d.K);
+  typename P::WT w;
+  typename P::COffsets co;
+  co.load(threadIdx.x, d.t, m0, n0, int(d.M), int(d.N));
+  P::accumulate(w, packed::buffer_of(d.A, d.bytesA), packed::buffer_of(d.B, d.bytesB), d.am + m0, d.ak, d.bk,
+                d.bn + n0, 0, (K + P::BK - 1) / P::BK, to_lds(smem), co, to_lds(ctab));
+  // plain stores: the segments of many outputs are shorter than a cache line
+  gett_store_staged<T, T, P::BM, P::BN, P::WGM, P::WGN, false, false>(w, static_cast<T *>(d.C), to_lds(ctab),
+                                                                      to_lds(ctab) + P::BM, d.M, d.N, d.alpha,
+                                                                      d.beta, m0, n0);
+}
+
+template <typename T, int CLS>
+__device__ __forceinline__ void packed_cls(const BatchDesc &d, int tile, T *smem, int64_t *ctab) {
+  switch (d.variant & 3) {
+    case 0: packed_item<T, CLS, 0, 0>(d, tile, smem, ctab); break;
+    case 1: packed_item<T, CLS, 0, 1>(d, tile, smem, ctab); break;
+    case 2: packed_item<T, CLS, 1, 0>(d, tile, smem, ctab); break;
+    default: packed_item<T, CLS, 1, 1>(d, tile, smem, ctab); break;
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256, 2) void batch_packed_kernel(const BatchDesc *__restrict__ descs,
+                                                              const BatchItem *__restrict__ items, BatchQueues q,
+                                                              int *__restrict__ counters) {
+  typedef BatchCore<T, packed_class_ok(3, sizeof(T) == 8 ? 0 : 1) ? 3 : 1, 0, 0> Largest;
+  __shared__ __attribute__((aligned(16))) T smem[Largest::LDS];
+  __shared__ int64_t ctab[256];
+  __shared__ int s_item;
+  // the XCD this workgroup runs on (workgroups are dealt to the XCDs in turn)
+  int queue = int(blockIdx.x % kBatchQueues);
+  // thread 0 holds the next item of the queue, taken while the current one runs
+  int next = 0;
+  if (threadIdx.x == 0) next = atomicAdd(&counters[queue], 1);
+  for (int drained = 0; drained < kBatchQueues;) {
+    const int64_t len = q.off[queue + 1] - q.off[queue];
+    if (threadIdx.x == 0) s_item = next;
+    __syncthreads();   // (also: the last item's LDS is free)
+    const int64_t item = __builtin_amdgcn_readfirstlane(s_item);
+    if (item >= len) {   // this queue is drained (its counter only grows): the next one
+      queue = (queue + 1) % kBatchQueues;
+      ++drained;
+      if (threadIdx.x == 0 && drained < kBatchQueues) next = atomicAdd(&counters[queue], 1);
+      __syncthreads();
+      continue;
+    }
+    if (threadIdx.x == 0) next = atomicAdd(&counters[queue], 1);
+    const BatchItem w = items[q.off[queue] + item];
+    const BatchDesc d = descs[__builtin_amdgcn_readfirstlane(w.problem)];
+    switch (d.cls) {
+      case 1: packed_cls<T, 1>(d, w.tile, smem, ctab); break;
+      case 2: packed_cls<T, 2>(d, w.tile, smem, ctab); break;
+      case 3: if constexpr (sizeof(T) == 4) packed_cls<T, 3>(d, w.tile, smem, ctab); break;
+      default: packed_cls<T, 0>(d, w.tile, smem, ctab); break;
+    }
+    __syncthreads();   // s_item and the C offsets are read before they are written again
+  }
+}
+
 __global__ void reset_counters_kernel(int *counters) {
   if (threadIdx.x < kBatchQueues) counters[threadIdx.x] = 0;
 }
@@ -308,13 +388,16 @@ void batch_class_shape(int cls, int *bm, int *bn) {
 }
 
 bool batch_class_valid(int cls, int dtype, int mode, bool vec) {
-  return cls >= 0 && cls < kBatchClasses && class_ok(cls, dtype, mode, vec);
+  return cls >= 0 && cls < kBatchClasses && (mode == 2 ? packed_class_ok(cls, dtype) : class_ok(cls, dtype, mode, vec));
 }
 
 int batch_blocks_per_cu(int dtype, int mode) {
   int n = 0;
   hipError_t e;
-  if (mode == 1)
+  if (mode == 2)
+    e = dtype == 0 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_packed_kernel<double>, 256, 0)
+                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_packed_kernel<float>, 256, 0);
+  else if (mode == 1)
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<float, 1>, BatchWaves<1>::NT, 0);
   else if (dtype == 0)
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<double, 0>, NT, 0);
@@ -327,7 +410,12 @@ hipError_t launch_batch(const BatchDesc *descs, const BatchItem *items, const Ba
                         int dtype, int mode, int grid, hipStream_t s) {
   hipLaunchKernelGGL(reset_counters_kernel, dim3(1), dim3(64), 0, s, counters);
   if (q.off[kBatchQueues] <= 0) return hipGetLastError();
-  if (mode == 1) {
+  if (mode == 2) {
+    if (dtype == 0)
+      hipLaunchKernelGGL(batch_packed_kernel<double>, dim3(grid), dim3(256), 0, s, descs, items, q, counters);
+    else
+      hipLaunchKernelGGL(batch_packed_kernel<float>, dim3(grid), dim3(256), 0, s, descs, items, q, counters);
+  } else if (mode == 1) {
     if (dtype != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL((batch_kernel<float, 1>), dim3(grid), dim3(BatchWaves<1>::NT), 0, s, descs, items, q,
                        counters);

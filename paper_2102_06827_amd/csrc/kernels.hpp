@@ -92,6 +92,10 @@ struct BatchDesc {
   int variant;         // layoutA * 2 + layoutB, + 4 for element (non-vector) loads
   int cls;             // tile class (batch_class_shape); element loads: class 0 only
   int tilesN;          // output tiles of the class along N
+  // mode 2: the packed kernel's byte offset tables (see PackedLaunch) and the
+  // operands' spans
+  const uint32_t *am, *ak, *bk, *bn;
+  uint32_t bytesA, bytesB;
 };
 struct BatchItem {
   int problem;
@@ -109,9 +113,10 @@ struct BatchQueues {
 constexpr int kBatchClasses = 4;
 void batch_class_shape(int cls, int *bm, int *bn);
 // whether tile class `cls` is compiled for storage dtype (0 = FP64, 1 = FP32),
-// mode (0: native MFMA, 1: fused BF16x3) and vector or element loads
+// mode (0, 2: native MFMA, 1: fused BF16x3) and vector or element loads
 bool batch_class_valid(int cls, int dtype, int mode, bool vec);
-// mode 0: native MFMA of the storage type; 1: fused BF16x3 (FP32 storage).
+// mode 0: native MFMA of the storage type, vector loads where a problem allows
+// them; 1: fused BF16x3 (FP32 storage); 2: native MFMA, packed element loads.
 // counters: kBatchQueues ints (reset inside the launch sequence).
 hipError_t launch_batch(const BatchDesc *descs, const BatchItem *items, const BatchQueues &q, int *counters,
                         int dtype, int mode, int grid, hipStream_t s);
@@ -195,5 +200,14 @@ struct PermuteLaunch {
   double fill = 0.0;   // with alpha == 0: out = fill + beta * out
 };
 hipError_t launch_permute(const PermuteLaunch &p, hipStream_t s);
+
+// Many dense copies in one launch.  permute_copy_entry writes the entry of p
+// (permute_copy_stride() bytes, for device memory) and returns its workgroups,
+// the first of them number `first` of the launch; 0 if p is not a transpose
+// with alpha = 1 and beta = 0 of fewer than 2^30 elements (then it needs a
+// launch of its own).
+int64_t permute_copy_entry(const PermuteLaunch &p, int64_t first, void *entry);
+size_t permute_copy_stride();
+hipError_t launch_permute_copies(const void *entries, int n, int64_t blocks, int dtype, hipStream_t s);
 
 }  // namespace comet

@@ -150,3 +150,37 @@ def test_switched_off(monkeypatch):
     monkeypatch.setenv("COMET_PACKED", "0")
     A = torch.zeros((75, 75), dtype=torch.float64, device="cuda")
     assert comet.Plan("ij=ik*kj", A, A.clone()).describe()["packed"] == 0
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("cls", [None, "0", "1", "2", "3"])
+def test_batch_of_odd_problems(cls, dtype, monkeypatch):
+    """The batch on the packed tile product: odd extents in every tile class,
+    batch labels, a dense copy of an operand (all of them in one launch),
+    an empty summation and alpha = 0 beside them, run twice."""
+    if cls is not None:
+        monkeypatch.setenv("COMET_BATCH_CLASS", cls)
+    rng = np.random.default_rng(9500)
+    host = []
+    for t, spec in enumerate(["abij=acik*bkcj", "abij=ciak*bkjc", "ajbi=kcia*cjkb", "bij=bik*bkj", "abij=ciak*bkjc",
+                              "abij=ijcd*cdab", "ij=ik*kj", "ij=ik*kj"]):
+        ext = {ch: int(rng.integers(3, 21)) for ch in set(spec) - set("=*")}
+        if t == 6:
+            ext["k"] = 0
+        A, B, C0 = inputs(spec, ext, 9500 + 10 * t, kind="integer", beta=True)
+        host.append((spec, A, B, C0, 0.0 if t == 7 else 2.0, 0.0 if t == 1 else -1.0))
+    dev = [dict(spec=s, A=torch_dev(A, DT[dtype]), B=torch_dev(B, DT[dtype]), C=torch_dev(C0, DT[dtype]), alpha=al,
+                beta=be) for s, A, B, C0, al, be in host]
+    print_case("packed batch", dtype, cls)
+    bt = comet.Batch(dev, dtype=DT[dtype])
+    d = bt.describe()
+    assert d["copies"] >= 2
+    if cls in ("0", "1", "2"):
+        assert d["classes"][int(cls)] > 0
+    want = [C0 for _, _, _, C0, _, _ in host]
+    for _ in range(2):
+        bt()
+        torch.cuda.synchronize()
+        want = [oracle.contract(s, A, B, C, alpha=al, beta=be) for (s, A, B, _, al, be), C in zip(host, want)]
+        for (s, *_), x, ref in zip(host, dev, want):
+            assert np.array_equal(to_np(x["C"]), ref), s
