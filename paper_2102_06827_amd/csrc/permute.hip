@@ -227,53 +227,112 @@ struct TileArgs {
   int64_t tiles_i, tiles_o;
 };
 
-// One 32 x 32 tile, number bid of the permutation.
-template <typename T, typename I>
+// One E x E tile, number bid of the permutation, by TP x TR threads: E / TP
+// elements along a row a thread, rows TR apart.
+template <typename T, typename I, int E>
 __device__ __forceinline__ void permute_tile(const T *__restrict__ in, T *__restrict__ out, const TileArgs &a,
-                                             int64_t bid, double alpha, double beta, T (*tile)[TP + 1],
+                                             int64_t bid, double alpha, double beta, T (*tile)[E + 1],
                                              int64_t *gi_out, int64_t *go_in) {
   typedef typename std::conditional<sizeof(T) == 8, double, float>::type Te;
   const I b0 = I(bid), b1 = b0 / I(a.tiles_i), b2 = b1 / I(a.tiles_o);
   const int64_t ti = int64_t(b0 - b1 * I(a.tiles_i)), to = int64_t(b1 - b2 * I(a.tiles_o));
   int64_t bi, bo;
   decompose<I>(a.batch, int64_t(b2), &bi, &bo);
-  const int64_t i0 = ti * TP, o0 = to * TP;
-  const int x = threadIdx.x, y = threadIdx.y;
-  if (y == 0) {
+  const int64_t i0 = ti * E, o0 = to * E;
+  constexpr int ROWS = TP * TR / E;   // rows a pass covers
+  const int tid = threadIdx.y * TP + threadIdx.x;
+  const int x = tid % E, y = tid / E;
+  if (tid < 2 * E) {
     int64_t di, dout;
-    decompose<I>(a.gi, i0 + x < a.EI ? i0 + x : 0, &di, &dout);
-    gi_out[x] = dout;
-  } else if (y == 1) {
-    int64_t di, dout;
-    decompose<I>(a.go, o0 + x < a.EO ? o0 + x : 0, &di, &dout);
-    go_in[x] = di;
+    if (tid < E) {
+      decompose<I>(a.gi, i0 + x < a.EI ? i0 + x : 0, &di, &dout);
+      gi_out[x] = dout;
+    } else {
+      decompose<I>(a.go, o0 + x < a.EO ? o0 + x : 0, &di, &dout);
+      go_in[x] = di;
+    }
   }
   __syncthreads();
+  // every load in flight before the first is stored
+  T v[E / ROWS];
 #pragma unroll
-  for (int r = 0; r < TP; r += TR) {
+  for (int r = 0; r < E; r += ROWS) {
     const int64_t i = i0 + x, o = o0 + y + r;
-    if (alpha != 0.0 && i < a.EI && o < a.EO) tile[x][y + r] = in[bi + i * a.gi_sin + go_in[y + r]];
+    v[r / ROWS] = (alpha != 0.0 && i < a.EI && o < a.EO) ? in[bi + i * a.gi_sin + go_in[y + r]] : T(0);
   }
+#pragma unroll
+  for (int r = 0; r < E; r += ROWS) tile[x][y + r] = v[r / ROWS];
   __syncthreads();
   const Te al = Te(alpha), be = Te(beta);
 #pragma unroll
-  for (int r = 0; r < TP; r += TR) {
+  for (int r = 0; r < E; r += ROWS) {
     const int64_t o = o0 + x, i = i0 + y + r;
     if (i < a.EI && o < a.EO) {
       const int64_t addr = bo + o * a.go_sout + gi_out[y + r];
-      Te v = alpha != 0.0 ? al * Te(tile[y + r][x]) : Te(0);
-      if (beta != 0.0) v = v + be * Te(out[addr]);
-      out[addr] = T(v);   // a plain store: nontemporal ones made this kernel 18% slower
+      Te w = alpha != 0.0 ? al * Te(tile[y + r][x]) : Te(0);
+      if (beta != 0.0) w = w + be * Te(out[addr]);
+      out[addr] = T(w);   // a plain store: nontemporal ones made this kernel 18% slower
     }
   }
 }
 
-template <typename T, typename I>
+template <typename T, typename I, int E>
 __global__ __launch_bounds__(TP *TR) void permute_tiled(const T *__restrict__ in, T *__restrict__ out, TileArgs a,
                                                          double alpha, double beta) {
-  __shared__ T tile[TP][TP + 1];
-  __shared__ int64_t gi_out[TP], go_in[TP];
-  permute_tile<T, I>(in, out, a, blockIdx.x, alpha, beta, tile, gi_out, go_in);
+  __shared__ T tile[E][E + 1];
+  __shared__ int64_t gi_out[E], go_in[E];
+  permute_tile<T, I, E>(in, out, a, blockIdx.x, alpha, beta, tile, gi_out, go_in);
+}
+
+// Groups of at most 16 elements: a wave per 16 x 16 tile, four tiles a
+// workgroup.  (An edge of 15 fills a fifth of a 32 x 32 tile: 126^2 x 15^2 in
+// FP64 27 us there.)
+constexpr int TS = 16;
+template <typename T, typename I>
+__global__ __launch_bounds__(256) void permute_small(const T *__restrict__ in, T *__restrict__ out, TileArgs a,
+                                                     int64_t tiles, double alpha, double beta) {
+  typedef typename std::conditional<sizeof(T) == 8, double, float>::type Te;
+  __shared__ T tile_s[4][TS][TS + 1];
+  __shared__ int64_t gi_s[4][TS], go_s[4][TS];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t bid = int64_t(blockIdx.x) * 4 + wave;
+  const int x = lane % TS, y = lane / TS;
+  const bool any = bid < tiles;
+  const I b0 = I(any ? bid : 0), b1 = b0 / I(a.tiles_i), b2 = b1 / I(a.tiles_o);
+  const int64_t i0 = int64_t(b0 - b1 * I(a.tiles_i)) * TS, o0 = int64_t(b1 - b2 * I(a.tiles_o)) * TS;
+  int64_t bi, bo;
+  decompose<I>(a.batch, int64_t(b2), &bi, &bo);
+  if (y < 2) {
+    int64_t di, dout;
+    if (y == 0) {
+      decompose<I>(a.gi, i0 + x < a.EI ? i0 + x : 0, &di, &dout);
+      gi_s[wave][x] = dout;
+    } else {
+      decompose<I>(a.go, o0 + x < a.EO ? o0 + x : 0, &di, &dout);
+      go_s[wave][x] = di;
+    }
+  }
+  __syncthreads();
+  T v[TS / 4];
+#pragma unroll
+  for (int r = 0; r < TS; r += 4) {
+    const int64_t i = i0 + x, o = o0 + y + r;
+    v[r / 4] = (any && alpha != 0.0 && i < a.EI && o < a.EO) ? in[bi + i * a.gi_sin + go_s[wave][y + r]] : T(0);
+  }
+#pragma unroll
+  for (int r = 0; r < TS; r += 4) tile_s[wave][x][y + r] = v[r / 4];
+  __syncthreads();
+  const Te al = Te(alpha), be = Te(beta);
+#pragma unroll
+  for (int r = 0; r < TS; r += 4) {
+    const int64_t o = o0 + x, i = i0 + y + r;
+    if (any && i < a.EI && o < a.EO) {
+      const int64_t addr = bo + o * a.go_sout + gi_s[wave][y + r];
+      Te w = alpha != 0.0 ? al * Te(tile_s[wave][y + r][x]) : Te(0);
+      if (beta != 0.0) w = w + be * Te(out[addr]);
+      out[addr] = T(w);
+    }
+  }
 }
 
 // Many transposes (alpha = 1, beta = 0) in one launch: workgroup b runs tile
@@ -300,7 +359,7 @@ __global__ __launch_bounds__(TP *TR) void permute_copies(const CopyEntry *__rest
       hi = mid - 1;
   }
   const CopyEntry &c = e[lo];
-  permute_tile<T, uint32_t>(static_cast<const T *>(c.in), static_cast<T *>(c.out), c.a, b - c.first, 1.0, 0.0, tile,
+  permute_tile<T, uint32_t, TP>(static_cast<const T *>(c.in), static_cast<T *>(c.out), c.a, b - c.first, 1.0, 0.0, tile,
                             gi_out, go_in);
 }
 
@@ -313,7 +372,7 @@ void fill(DimSet &s, const std::vector<PermDim> &d, const std::vector<int> &idx)
   }
 }
 
-TileArgs tile_args(const PermShape &sh) {
+TileArgs tile_args(const PermShape &sh, int E) {
   TileArgs a{};
   fill(a.gi, sh.d, sh.gi);
   fill(a.go, sh.d, sh.go);
@@ -322,8 +381,8 @@ TileArgs tile_args(const PermShape &sh) {
   a.EO = sh.EO;
   a.gi_sin = sh.d[sh.ui].si;
   a.go_sout = sh.d[sh.uo].so;
-  a.tiles_i = (sh.EI + TP - 1) / TP;
-  a.tiles_o = (sh.EO + TP - 1) / TP;
+  a.tiles_i = (sh.EI + E - 1) / E;
+  a.tiles_o = (sh.EO + E - 1) / E;
   return a;
 }
 int64_t tile_blocks(const PermShape &sh, const TileArgs &a) {
@@ -386,15 +445,43 @@ hipError_t launch_perm_t(const PermuteLaunch &p, hipStream_t s) {
       hipLaunchKernelGGL((permute_stream<T, 1, uint64_t>), dim3(grid), dim3(SB), 0, s, in, out, a, p.alpha, p.beta);
     return hipGetLastError();
   }
-  // transpose over the groups Gi and Go
-  const TileArgs a = tile_args(sh);
-  const int64_t blocks = tile_blocks(sh, a);
-  if (total < (int64_t(1) << 30))
-    hipLaunchKernelGGL((permute_tiled<T, uint32_t>), dim3(unsigned(blocks)), dim3(TP, TR), 0, s, in, out, a, p.alpha,
-                       p.beta);
+  // transpose over the groups Gi and Go.
+  // The tile edge: 16 where a group holds no more, else 64 where that pads
+  // little more than 32 and leaves a tile for every CU.  MI355X, cold: 99^2 x
+  // 33^2 in FP64 41 us (32: 49), 6788 x 4772 99 (108), 128^2 x 40^2 80 (141);
+  // FP32 25 (31), 59 (69) and 45 (104) -- a 64-wide row cuts fewer cache lines
+  // at its ends and keeps more loads in flight; 96^2 x 32^2 in FP64 31 (29).
+  const bool small = total < (int64_t(1) << 30);
+  if (std::min(sh.EI, sh.EO) <= TS) {
+    const TileArgs a = tile_args(sh, TS);
+    const int64_t tiles = tile_blocks(sh, a), groups = (tiles + 3) / 4;
+    const int64_t whole = tile_blocks(sh, tile_args(sh, TP));
+    if (tiles < 4 * whole && groups < (int64_t(1) << 24)) {
+      if (small)
+        hipLaunchKernelGGL((permute_small<T, uint32_t>), dim3(unsigned(groups)), dim3(256), 0, s, in, out, a, tiles,
+                           p.alpha, p.beta);
+      else
+        hipLaunchKernelGGL((permute_small<T, uint64_t>), dim3(unsigned(groups)), dim3(256), 0, s, in, out, a, tiles,
+                           p.alpha, p.beta);
+      return hipGetLastError();
+    }
+  }
+  const TileArgs a = tile_args(sh, TP), a64 = tile_args(sh, 64);
+  const int64_t blocks = tile_blocks(sh, a), blocks64 = tile_blocks(sh, a64);
+  const dim3 block(TP, TR);
+  if (sh.EI > TP && sh.EO > TP && 100 * blocks64 <= 115 * blocks / 4 && blocks64 >= 256) {
+    const dim3 grid(static_cast<unsigned>(blocks64));
+    if (small)
+      hipLaunchKernelGGL((permute_tiled<T, uint32_t, 64>), grid, block, 0, s, in, out, a64, p.alpha, p.beta);
+    else
+      hipLaunchKernelGGL((permute_tiled<T, uint64_t, 64>), grid, block, 0, s, in, out, a64, p.alpha, p.beta);
+    return hipGetLastError();
+  }
+  const dim3 grid(static_cast<unsigned>(blocks));
+  if (small)
+    hipLaunchKernelGGL((permute_tiled<T, uint32_t, TP>), grid, block, 0, s, in, out, a, p.alpha, p.beta);
   else
-    hipLaunchKernelGGL((permute_tiled<T, uint64_t>), dim3(unsigned(blocks)), dim3(TP, TR), 0, s, in, out, a, p.alpha,
-                       p.beta);
+    hipLaunchKernelGGL((permute_tiled<T, uint64_t, TP>), grid, block, 0, s, in, out, a, p.alpha, p.beta);
   return hipGetLastError();
 }
 
@@ -408,7 +495,7 @@ int64_t permute_copy_entry(const PermuteLaunch &p, int64_t first, void *entry) {
   const PermShape sh = permute_shape(p.ndim, p.ext, p.s_in, p.s_out, true);
   if (sh.kind != PERM_TILED || p.alpha != 1.0 || p.beta != 0.0 || sh.total >= (int64_t(1) << 30)) return 0;
   CopyEntry c;
-  c.a = tile_args(sh);
+  c.a = tile_args(sh, TP);
   c.in = p.in;
   c.out = p.out;
   c.first = first;
