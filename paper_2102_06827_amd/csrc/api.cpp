@@ -161,20 +161,6 @@ void packed_table(const std::vector<int64_t> &t, bool rows, size_t es, uint32_t 
   for (size_t j = n; j < len; ++j) out[j] = rows ? out[n - 1] : kPackedOut;
 }
 
-// Whether C's offsets come in whole 64-byte segments along n, aligned to 64
-// bytes from C's base.
-bool c_segments(const Analysis &an) {
-  const int64_t w = 64 / int64_t(elem_size(an.dtype));
-  if (an.n % w) return false;
-  for (int64_t m : an.offCm)
-    if (m % w) return false;
-  for (size_t j = 0; j < an.offCn.size(); ++j)
-    if (j % w ? an.offCn[j] != an.offCn[j - 1] + 1 : an.offCn[j] % w != 0) return false;
-  for (int64_t x : an.offCx)
-    if (x % w) return false;
-  return true;
-}
-
 comet_status_t upload_tables(comet_plan_s *p) {
   const Analysis &an = p->an;
   const std::vector<int64_t> *tabs[9] = {&an.offAm, &an.offAk, &an.offBk, &an.offBn, &an.offCm,
@@ -567,7 +553,6 @@ void even_choice(const Analysis &an, int cus, bool vecA, bool vecB, Schedule &sc
 // 1 GB of stores one after the other.  Returns its workgroups, 0 if not
 // taken; COMET_GETT_SHORTK=0 / 1 turns it off / on where it exists.
 constexpr int kShortKMax = 32;
-bool c_segments(const Analysis &an);
 int shortk_choice(const Analysis &an, int cus, bool vecA, bool vecB, int forced_tile) {
   const bool native = an.compute == COMET_COMPUTE_F64 || an.compute == COMET_COMPUTE_F32;
   const int dt = an.dtype == COMET_F64 ? 0 : 1, cp = an.compute == COMET_COMPUTE_F64 ? 0 : 1;
@@ -1208,8 +1193,8 @@ double time_us(F fn, hipStream_t s, bool *ok) {
   return best;
 }
 
-// The split products: time the slice-pair product's tiles -- 128 x 64 and
-// 192 x 192 for the classic splits (BF16x3, FP16x2) and, for FP32 storage in
+// The split products: time the slice-pair product's tiles -- the rule's
+// among the smaller ones and 192 x 192 for the classic splits (BF16x3, FP16x2) and, for FP32 storage in
 // BF16x3, the fused kernel; 128 x 64 and 128 x 96 for the aligned BF16
 // slices -- and record the fastest (entry tile 0, 1, or 2 for the fused
 // kernel or the 128 x 96 tile) per problem class and apply it.  Called with
@@ -2014,7 +1999,10 @@ comet_status_t comet_plan_describe(comet_plan_t plan, char *buf, size_t len) {
       res = tile_resident(plan->an, plan->an.tile, plan->vecA_tables, plan->vecB_tables);
     js.pop_back();
     js += ",\"resident\":" + std::to_string(res);
-    if (plan->split.ws_bytes > 0) js += ",\"split_tile\":" + std::to_string(plan->split.tile);
+    if (plan->split.ws_bytes > 0) {
+      js += ",\"split_tile\":" + std::to_string(plan->split.tile);
+      js += ",\"split_block\":\"" + std::to_string(plan->split.bm) + "x" + std::to_string(plan->split.bn) + "\"";
+    }
     js += std::string(",\"fused3\":") + (plan->fused3 ? "true" : "false");
     js += "}";
   }

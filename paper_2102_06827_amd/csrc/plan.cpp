@@ -121,6 +121,18 @@ double unit_steps(const std::vector<int64_t> &off) {
   return off.size() > 1 ? double(n) / double(off.size() - 1) : 0.0;
 }
 
+bool c_segments(const Analysis &an) {
+  const int64_t w = 64 / int64_t(elem_size(an.dtype));
+  if (an.n % w) return false;
+  for (int64_t m : an.offCm)
+    if (m % w) return false;
+  for (size_t j = 0; j < an.offCn.size(); ++j)
+    if (j % w ? an.offCn[j] != an.offCn[j - 1] + 1 : an.offCn[j] % w != 0) return false;
+  for (int64_t x : an.offCx)
+    if (x % w) return false;
+  return true;
+}
+
 int contiguous_run(const std::vector<int64_t> &off) {
   const int64_t n = (int64_t)off.size();
   for (int v = 8; v > 1; v /= 2) {

@@ -161,6 +161,9 @@ PermuteDesc make_permute(const std::string &out_labels, const std::vector<int64_
 int contiguous_run(const std::vector<int64_t> &off);
 // The share of a table's steps that are 1.
 double unit_steps(const std::vector<int64_t> &off);
+// Whether C's offsets come in whole 64-byte segments along n, aligned to 64
+// bytes from C's base.
+bool c_segments(const Analysis &an);
 
 std::string describe_json(const Analysis &an);
 

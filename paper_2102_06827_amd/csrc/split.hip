@@ -40,6 +40,7 @@
 // v_mfma_i32_16x16x64_i8.
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 
@@ -543,8 +544,8 @@ template <typename Tout, int BM, int BN, int FM, int FN, int NTH, typename ValF>
 __device__ __forceinline__ void split_store(Tout *__restrict__ C, const int64_t *__restrict__ offCm,
                                             const int64_t *__restrict__ offCn, const int *__restrict__ eA,
                                             const int *__restrict__ eB, int64_t M, int64_t N, double alpha,
-                                            double beta, int64_t m0, int64_t n0, int wm0, int wn0, void *smem,
-                                            ValF val) {
+                                            double beta, int64_t m0, int64_t n0, int wm0, int wn0, int stream,
+                                            void *smem, ValF val) {
   typedef typename std::conditional<sizeof(Tout) == 8, double, float>::type Te;
   lds_t<int64_t> *const toff = to_lds(static_cast<int64_t *>(smem));
   lds_t<int> *const texp = to_lds(reinterpret_cast<int *>(static_cast<int64_t *>(smem) + BM + BN));
@@ -571,38 +572,50 @@ __device__ __forceinline__ void split_store(Tout *__restrict__ C, const int64_t 
     const double prod = (em == kExpNone || en == kExpNone) ? 0.0 : ldexp(val(i, j, r), em + en);
     return Te(alpha * prod);
   };
-  if (beta == 0.0) {
+  auto pass = [&](auto streamed) {
+    auto put = [&](Tout v, int64_t at) {
+      if constexpr (decltype(streamed)::value)
+        __builtin_nontemporal_store(v, &gC[at]);
+      else
+        gC[at] = v;
+    };
+    if (beta == 0.0) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int j = g / FM, i = g % FM;
+        int64_t a[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[r] = toff[ml(i, r)] + toff[BM + nl(j)];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (inside(i, r, j)) put(Tout(value(i, j, r)), a[r]);
+      }
+      return;
+    }
+    Tout cv[2][4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) cv[0][r] = gC[toff[ml(0, r)] + toff[BM + nl(0)]];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const int j = g / FM, i = g % FM;
+      __builtin_amdgcn_sched_barrier(0);
+      if (g + 1 < G) {
+        const int j1 = (g + 1) / FM, i1 = (g + 1) % FM;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) cv[(g + 1) & 1][r] = gC[toff[ml(i1, r)] + toff[BM + nl(j1)]];
+      }
       int64_t a[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) a[r] = toff[ml(i, r)] + toff[BM + nl(j)];
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (inside(i, r, j)) __builtin_nontemporal_store(Tout(value(i, j, r)), &gC[a[r]]);
+        if (inside(i, r, j)) put(Tout(value(i, j, r) + Te(beta) * Te(cv[g & 1][r])), a[r]);
     }
-    return;
-  }
-  Tout cv[2][4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) cv[0][r] = gC[toff[ml(0, r)] + toff[BM + nl(0)]];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const int j = g / FM, i = g % FM;
-    __builtin_amdgcn_sched_barrier(0);
-    if (g + 1 < G) {
-      const int j1 = (g + 1) / FM, i1 = (g + 1) % FM;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) cv[(g + 1) & 1][r] = gC[toff[ml(i1, r)] + toff[BM + nl(j1)]];
-    }
-    int64_t a[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) a[r] = toff[ml(i, r)] + toff[BM + nl(j)];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (inside(i, r, j)) __builtin_nontemporal_store(Tout(value(i, j, r) + Te(beta) * Te(cv[g & 1][r])), &gC[a[r]]);
-  }
+  };
+  if (stream)
+    pass(std::true_type{});
+  else
+    pass(std::false_type{});
 }
 
 template <typename ST, typename Tout, int MODE, int S>
@@ -611,7 +624,7 @@ __global__ __launch_bounds__(GNT) void split_gemm_kernel(const ST *__restrict__ 
                                                           Tout *__restrict__ C, const int64_t *__restrict__ offCm,
                                                           const int64_t *__restrict__ offCn, int64_t M, int64_t N,
                                                           int64_t Mp, int64_t Np, int64_t Kp, double alpha,
-                                                          double beta, int tilesM, int tilesN) {
+                                                          double beta, int tilesM, int tilesN, int stream) {
   typedef Pairs<MODE, S> PP;
   typedef typename Vec8<ST>::type v8;
   constexpr int WM = GBM / GWM, WN = GBN / GWN;      // 32 x 32
@@ -771,7 +784,7 @@ __global__ __launch_bounds__(GNT) void split_gemm_kernel(const ST *__restrict__ 
 
   // epilogue: C = alpha * 2^(eA + eB) * acc + beta * C
   static_assert((GBM + GBN) * 12 <= STAGE * int(sizeof(ST)), "epilogue tables fit in LDS");
-  split_store<Tout, GBM, GBN, FM, FN, GNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0,
+  split_store<Tout, GBM, GBN, FM, FN, GNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, stream,
                                           NBUF == 2 ? static_cast<void *>(smem0_) : static_cast<void *>(smem),
                                           [&](int i, int j, int r) { return acc64[i][j][r]; });
 }
@@ -785,22 +798,46 @@ __global__ __launch_bounds__(GNT) void split_gemm_kernel(const ST *__restrict__ 
 // above: 2), which takes the kernel off the LDS read limit, and a 3072^2
 // output is exactly 256 tiles, one per CU.
 
-constexpr int XBM = 192, XBN = 192;            // block tile
-constexpr int XWM = 2, XWN = 4;                // wave grid
-constexpr int XNT = 64 * XWM * XWN;
+// On products that do not fill whole rounds of 192 x 192 tiles the same
+// kernel runs smaller ones: 128 x 128 by 8 waves, 96 x 96 and 64 x 64 by 4
+// waves with two or three workgroups sharing a CU (in LDS at S = 3).
+// split_shape() chooses: 1452^3 in BF16x3 is 256 tiles of 96 x 96 (40 us
+// instead of 63 by 276 tiles of 128 x 64), 1725^3 730 of 64 x 64 (99 us with
+// the slicers instead of 156 by 81 of 192 x 192), 2048^3 256 of 128 x 128
+// (120 instead of 179), and 700^2 x 6000 121 of 64 x 64 (149 instead of 178).
+struct SplitShape {
+  int bm, bn, wgm, wgn;   // block tile, wave grid
+  // measured on MI355X, [0] for BF16x3 and [1] for FP16x2: workgroups a CU
+  // holds, us per 32-index stage of one workgroup alone on its CU, and us per
+  // stage and workgroup of a full CU
+  int wgs[2];
+  double alone[2], full[2];
+};
+constexpr SplitShape kSplitShapes[] = {
+    {128, 64, 4, 2, {2, 3}, {0.72, 0.49}, {0.610, 0.360}},   // 0: split_gemm_kernel
+    {192, 192, 2, 4, {1, 1}, {1.95, 1.15}, {2.22, 1.27}},    // 1
+    {128, 128, 2, 4, {1, 2}, {0.95, 0.60}, {1.07, 0.600}},   // 2
+    {96, 96, 2, 2, {2, 3}, {0.70, 0.56}, {0.655, 0.375}},    // 3
+    {64, 64, 2, 2, {3, 5}, {0.50, 0.40}, {0.335, 0.200}},    // 4
+};
+constexpr double kSplitStoreUs[2] = {0.34e-3, 0.2e-3};   // per output of a CU's workgroups: FP64, FP32
 
-template <typename ST, typename Tout, int MODE, int S>
-__global__ __launch_bounds__(XNT) void split_gemm_big_kernel(const ST *__restrict__ As, const ST *__restrict__ Bs,
+template <typename ST, typename Tout, int MODE, int S, int SHAPE>
+__global__ __launch_bounds__(64 * kSplitShapes[SHAPE].wgm * kSplitShapes[SHAPE].wgn,
+                             kSplitShapes[SHAPE].wgm * kSplitShapes[SHAPE].wgn * kSplitShapes[SHAPE].wgs[0] / 4) void
+split_gemm_big_kernel(const ST *__restrict__ As, const ST *__restrict__ Bs,
                                                               const int *__restrict__ eA, const int *__restrict__ eB,
                                                               Tout *__restrict__ C, const int64_t *__restrict__ offCm,
                                                               const int64_t *__restrict__ offCn, int64_t M, int64_t N,
                                                               int64_t Mp, int64_t Np, int64_t Kp, double alpha,
-                                                              double beta, int tilesM, int tilesN) {
+                                                              double beta, int tilesM, int tilesN, int stream) {
+  constexpr int XBM = kSplitShapes[SHAPE].bm, XBN = kSplitShapes[SHAPE].bn;
+  constexpr int XWM = kSplitShapes[SHAPE].wgm, XWN = kSplitShapes[SHAPE].wgn, XNT = 64 * XWM * XWN;
   typedef Pairs<MODE, S> PP;
   static_assert(PP::FOLD == 0, "the large tile keeps FP32 accumulators only");
   typedef typename Vec8<ST>::type v8;
-  constexpr int WM = XBM / XWM, WN = XBN / XWN;      // 96 x 48
-  constexpr int FM = WM / 16, FN = WN / 16;          // 6 x 3
+  constexpr int WM = XBM / XWM, WN = XBN / XWN;
+  constexpr int FM = WM / 16, FN = WN / 16;
   constexpr int STAGE = S * (XBM + XBN) * GBK;       // elements per LDS buffer
   static_assert(2 * STAGE * int(sizeof(ST)) <= 160 * 1024, "two stages must fit in LDS");
   // two buffers as two objects, so that the compiler can tell the loads
@@ -891,7 +928,7 @@ __global__ __launch_bounds__(XNT) void split_gemm_big_kernel(const ST *__restric
 
   // epilogue: C = alpha * 2^(eA + eB) * sum_a scale(a) * acc[a] + beta * C
   static_assert((XBM + XBN) * 12 <= STAGE * int(sizeof(ST)), "epilogue tables fit in LDS");
-  split_store<Tout, XBM, XBN, FM, FN, XNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, smem0_,
+  split_store<Tout, XBM, XBN, FM, FN, XNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, stream, smem0_,
                                           [&](int i, int j, int r) {
                                             double sum = 0.0;
 #pragma unroll
@@ -931,7 +968,7 @@ __global__ __launch_bounds__(WNT) void split_gemm_wide_kernel(const ST *__restri
                                                                Tout *__restrict__ C, const int64_t *__restrict__ offCm,
                                                                const int64_t *__restrict__ offCn, int64_t M, int64_t N,
                                                                int64_t Mp, int64_t Np, int64_t Kp, double alpha,
-                                                               double beta, int tilesM, int tilesN) {
+                                                               double beta, int tilesM, int tilesN, int stream) {
   typedef Pairs<MODE, S> PP;
   static_assert(MODE == 0 && PP::NACC == 3 && PP::FOLD == 4, "the wide tile is for the aligned split");
   static_assert(wide_tile_fits(S), "two stages must fit in LDS");
@@ -1098,7 +1135,7 @@ __global__ __launch_bounds__(WNT) void split_gemm_wide_kernel(const ST *__restri
   // (the last stage's barrier passed: both buffers are free, the clamped
   // loads past the end landed)
   static_assert((WBM + WBN) * 12 <= STAGE * int(sizeof(ST)), "epilogue tables fit in LDS");
-  split_store<Tout, WBM, WBN, FM, FN, WNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, smem0_,
+  split_store<Tout, WBM, WBN, FM, FN, WNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, stream, smem0_,
                                           [&](int i, int j, int r) { return acc64[i][j][r]; });
 }
 
@@ -1252,7 +1289,7 @@ __global__ __launch_bounds__(GNT) void split_gemm_i8_kernel(const signed char *_
   // (after an odd last stage, buffer 0 is still being read: wait for every
   // wave before its first bytes take the epilogue tables)
   if constexpr (NBUF == 2) __syncthreads();
-  split_store<Tout, GBM, GBN, FM, FN, GNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0,
+  split_store<Tout, GBM, GBN, FM, FN, GNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, 1,
                                           NBUF == 2 ? static_cast<void *>(smem0_) : static_cast<void *>(smem),
                                           [&](int i, int j, int r) {
                                             double sum = 0.0;
@@ -1293,6 +1330,10 @@ hipError_t run_split(const Analysis &an, const SplitPlan &sp, const GettTables &
   hipLaunchKernelGGL((split_pack_kernel<Tin, ST, MODE, S>), dim3(unsigned(packs)), dim3(PT), 0, s, a);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   const int tilesM = int(sp.Mp / GBM), tilesN = int(sp.Np / GBN);
+  // C past the caches (nontemporal stores) where it comes in whole 64-byte
+  // segments; a segment stored in parts that way costs a memory round trip
+  // for each (a 192 x 192 tile's FP64 epilogue: 43 us, 14 through the caches)
+  const int stream = sp.segments && reinterpret_cast<uintptr_t>(C) % 64 == 0;
   if constexpr (MODE == 3) {
     // exact int32 diagonal sums over at most IKC indices per launch; later
     // launches add into C
@@ -1306,22 +1347,34 @@ hipError_t run_split(const Analysis &an, const SplitPlan &sp, const GettTables &
     if constexpr (MODE == 0 && wide_tile_fits(S)) {
       hipLaunchKernelGGL((split_gemm_wide_kernel<ST, Tin, MODE, S>), dim3(int(sp.Mp / WBM) * int(sp.Np / WBN)),
                          dim3(WNT), 0, s, As, Bs, eA, eB, static_cast<Tin *>(C), t.offCm, t.offCn, an.m, an.n, sp.Mp,
-                         sp.Np, sp.Kp, alpha, beta, int(sp.Mp / WBM), int(sp.Np / WBN));
+                         sp.Np, sp.Kp, alpha, beta, int(sp.Mp / WBM), int(sp.Np / WBN), stream);
     } else {
       return hipErrorInvalidValue;
     }
-  } else if (sp.tile == 1) {
+  } else if (sp.shape > 0) {
     if constexpr (Pairs<MODE, S>::FOLD == 0) {
-      hipLaunchKernelGGL((split_gemm_big_kernel<ST, Tin, MODE, S>), dim3(int(sp.Mp / XBM) * int(sp.Np / XBN)),
-                         dim3(XNT), 0, s, As, Bs, eA, eB, static_cast<Tin *>(C), t.offCm, t.offCn, an.m, an.n, sp.Mp,
-                         sp.Np, sp.Kp, alpha, beta, int(sp.Mp / XBM), int(sp.Np / XBN));
+      auto launch = [&](auto shape) {
+        constexpr SplitShape X = kSplitShapes[shape.value];
+        const int tm = int((an.m + X.bm - 1) / X.bm), tn = int((an.n + X.bn - 1) / X.bn);
+        hipLaunchKernelGGL((split_gemm_big_kernel<ST, Tin, MODE, S, shape.value>), dim3(tm * tn),
+                           dim3(64 * X.wgm * X.wgn), 0, s, As, Bs, eA, eB, static_cast<Tin *>(C), t.offCm, t.offCn,
+                           an.m, an.n, sp.Mp, sp.Np, sp.Kp, alpha, beta, tm, tn, stream);
+      };
+      if (sp.shape == 1)
+        launch(std::integral_constant<int, 1>{});
+      else if (sp.shape == 2)
+        launch(std::integral_constant<int, 2>{});
+      else if (sp.shape == 3)
+        launch(std::integral_constant<int, 3>{});
+      else
+        launch(std::integral_constant<int, 4>{});
     } else {
       return hipErrorInvalidValue;
     }
   } else
     hipLaunchKernelGGL((split_gemm_kernel<ST, Tin, MODE, S>), dim3(tilesM * tilesN), dim3(GNT), 0, s, As, Bs, eA,
                        eB, static_cast<Tin *>(C), t.offCm, t.offCn, an.m, an.n, sp.Mp, sp.Np, sp.Kp, alpha, beta,
-                       tilesM, tilesN);
+                       tilesM, tilesN, stream);
   return hipGetLastError();
 }
 
@@ -1352,6 +1405,45 @@ hipError_t dispatch(const Analysis &an, const SplitPlan &sp, const GettTables &t
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// Rows of a packed operand: whole tiles, and whole slicer tiles of PR.
+int64_t split_rows(int64_t rows, int64_t tile) { return round_up(round_up(rows, tile), PR); }
+
+// The tile of the classic splits (kSplitShapes) that the problem fits best:
+// the busiest CU's workgroups in rounds of as many as it holds, each stage
+// of a round at the measured rate (a round with few workgroups takes one
+// workgroup's own time), and their outputs' stores.  Its times lie within 8%
+// of the measured kernel over 64 to 1536 tiles of every shape.  `large`:
+// whether 192 x 192 tiles may be taken.  A shape whose slices need more
+// than kSplitScratch of workspace, which an execution without allocation may
+// not use, is taken only if every shape needs as much.
+constexpr int64_t kSplitScratch = int64_t(128) << 20;
+int split_shape(const Analysis &an, const SplitPlan &sp, bool large) {
+  const int x = sp.mode - 1;
+  const double stages = double(round_up(an.k, PK) / GBK);
+  int best = 0;
+  double best_us = 1e300;
+  bool best_fits = false;
+  for (int i = 0; i < int(sizeof(kSplitShapes) / sizeof(SplitShape)); ++i) {
+    const SplitShape &X = kSplitShapes[i];
+    if (i == 1 && !large) continue;
+    const double tiles = double(round_up(an.m, X.bm) / X.bm) * double(round_up(an.n, X.bn) / X.bn);
+    const double wgs = std::ceil(tiles / 256), rounds = std::floor(wgs / X.wgs[x]), rest = wgs - rounds * X.wgs[x];
+    double stage = rounds * X.wgs[x] * X.full[x];
+    if (rest > 0) stage += std::max(X.alone[x], rest * X.full[x]);
+    stage = std::max(stage, X.alone[x]);
+    const double us = stages * stage + wgs * X.bm * X.bn * kSplitStoreUs[an.dtype == COMET_F64 ? 0 : 1];
+    const double bytes = 2.0 * sp.S * double(round_up(an.k, PK)) *
+                         (double(split_rows(an.m, X.bm)) + double(split_rows(an.n, X.bn)));
+    const bool fits = bytes + (1 << 20) <= double(kSplitScratch);
+    if (fits == best_fits ? us < best_us : fits) {
+      best = i;
+      best_us = us;
+      best_fits = fits;
+    }
+  }
+  return best;
+}
+
 }  // namespace
 
 Status split_prepare(const Analysis &an, SplitPlan &sp, int force_tile) {
@@ -1365,15 +1457,12 @@ Status split_prepare(const Analysis &an, SplitPlan &sp, int force_tile) {
     return Status::error(COMET_ERR_UNSUPPORTED, "split slices must be within 3..6");
   if (sp.mode == 3 && (sp.S < 3 || sp.S > 8))
     return Status::error(COMET_ERR_UNSUPPORTED, "int8 split slices must be within 3..8");
-  // the large tile for the classic splits on large products, when padding
-  // to 192 wastes little (COMET_SPLIT_TILE=0/1 overrides)
+  // COMET_SPLIT_TILE=0/1 keeps the classic splits on 128 x 64 / 192 x 192 tiles
   sp.tile = 0;
   const char *env = std::getenv("COMET_SPLIT_TILE");
   if (sp.mode == 1 || sp.mode == 2) {
-    const double waste = double(round_up(an.m, XBM)) * double(round_up(an.n, XBN)) / (double(an.m) * double(an.n));
-    sp.tile = (an.m >= 1536 && an.n >= 1536 && waste <= 1.1) ? 1 : 0;
-    if (env && *env) sp.tile = std::atoi(env) == 1 ? 1 : 0;
-    if (force_tile >= 0) sp.tile = force_tile == 1 ? 1 : 0;
+    sp.shape = env && *env ? (std::atoi(env) == 1 ? 1 : 0) : force_tile == 1 ? 1 : split_shape(an, sp, force_tile != 0);
+    sp.tile = sp.shape == 1 ? 1 : 0;
   } else if (sp.mode == 0 && wide_tile_fits(sp.S)) {
     // the wide tile pads N to a multiple of 192 (its 96 and the slicer's 64)
     const double waste = double(round_up(an.m, WBM)) * double(round_up(an.n, 192)) / (double(an.m) * double(an.n));
@@ -1383,12 +1472,13 @@ Status split_prepare(const Analysis &an, SplitPlan &sp, int force_tile) {
     // its loads address a summation block of the slices with 32-bit offsets
     if (64.0 * sp.S * (double(round_up(an.m, WBM)) + double(round_up(an.n, 192))) >= 4294967296.0) sp.tile = 0;
   }
-  sp.Mp = round_up(an.m, sp.tile == 1 ? XBM : sp.tile == 2 ? WBM : GBM);
-  sp.Np = round_up(an.n, sp.tile == 1 ? XBN : sp.tile == 2 ? 192 : GBN);
+  const SplitShape &X = kSplitShapes[sp.shape];
+  sp.bm = sp.tile == 2 ? WBM : X.bm;
+  sp.bn = sp.tile == 2 ? WBN : X.bn;
+  sp.Mp = sp.tile == 2 ? round_up(an.m, WBM) : split_rows(an.m, X.bm);
+  sp.Np = sp.tile == 2 ? round_up(an.n, 192) : split_rows(an.n, X.bn);
   sp.Kp = round_up(an.k, PK);   // whole slicer tiles (a multiple of GBK and IBK)
-  const int64_t tiles = sp.tile == 1   ? (sp.Mp / XBM) * (sp.Np / XBN)
-                        : sp.tile == 2 ? (sp.Mp / WBM) * (sp.Np / WBN)
-                                       : (sp.Mp / GBM) * (sp.Np / GBN);
+  const int64_t tiles = (sp.Mp / sp.bm) * (sp.Np / sp.bn);   // (at least the launched ones)
   // one pack launch covers both operands' tiles; its grid must stay below
   // 2^32 work-items
   if (tiles > INT_MAX || ((sp.Mp + sp.Np) / PR) * (sp.Kp / PK) > int64_t(INT_MAX) / PT)
@@ -1417,6 +1507,7 @@ Status split_prepare(const Analysis &an, SplitPlan &sp, int force_tile) {
   sp.offPB = off;
   off = align256(off + size_t(sp.ky) * sp.Np * 4);
   sp.ws_bytes = off;
+  sp.segments = c_segments(an);
   return Status{};
 }
 

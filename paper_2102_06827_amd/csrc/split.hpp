@@ -17,12 +17,16 @@ struct SplitPlan {
   size_t offPA = 0, offPB = 0;                        // partial row exponents, ky per row
   int ky = 1;                                         // summation ranges of the exponent pass
   size_t ws_bytes = 0;
-  int tile = 0;             // slice-pair product: 0 the 128 x 64 tile, 1 the 192 x 192 tile (modes 1, 2),
-                            // 2 the 128 x 96 tile (mode 0, S <= 5)
+  int tile = 0;             // slice-pair product: 1 the 192 x 192 tile (modes 1, 2), 2 the 128 x 96 tile
+                            // (mode 0, S <= 5), 0 another (modes 0, 3: 128 x 64; modes 1, 2: `shape`)
+  bool segments = false;    // C is stored in whole 64-byte segments (c_segments)
+  int shape = 0;            // the block tile (an index of kSplitShapes in split.hip; 0 in modes 0 and 3)
+  int bm = 128, bn = 64;    // its rows and columns
 };
 
-// force_tile >= 0 sets the slice-pair tile (the autotuner's choice: 0 or 1
-// for modes 1 and 2, 0 or 2 for mode 0); otherwise a size rule, which
+// force_tile >= 0 sets the slice-pair tile (the autotuner's choice: for modes
+// 1 and 2, 1 for 192 x 192 or 0 for the rule's among the smaller ones; 0 or 2
+// for mode 0); otherwise a size rule, which
 // COMET_SPLIT_TILE overrides.
 Status split_prepare(const Analysis &an, SplitPlan &sp, int force_tile = -1);
 // vecA / vecB: the offset tables allow vector loads of the operand along its
