@@ -415,112 +415,51 @@ __device__ __forceinline__ int sw(int r, int c) { return r * GBK + ((c ^ ((r >> 
 // 16 rows; one load of 64 lanes x 16 bytes fills a block, lane L writing
 // bytes 16 L .. 16 L + 15 of it, i.e. row 16 g + L / 4 at chunk position
 // L mod 4, which holds the row's chunk (L mod 4) ^ ((row / 4) mod 4).  Wave w
-// of NW takes blocks w, w + NW, ...  A and B: the first row of each
-// operand's packed slices (64-byte rows in the blocked layout).  The
-// addresses do not depend on the stage but for its summation block's offset,
-// the same for A and B, so they are worked out once (init) and a stage is NU
-// loads (issue).  The loads are counted by the wave's vector-memory
-// counter: wait for it to reach zero, then a barrier, before the stage is
-// read.
+// of NW takes blocks w, w + NW, ..., every wave the same number (a wave short
+// of blocks loads the last one again, the same bytes to the same place).  A
+// and B: the first row of each operand's packed slices (64-byte rows in the
+// blocked layout).  The addresses do not depend on the stage but for its
+// summation block's offset, the same for A and B, so they are worked out once
+// (init), in scalar registers, and a stage is NU loads (issue).  The loads are
+// counted by the wave's vector-memory counter: wait for it to reach zero,
+// then a barrier, before the stage is read.
+//
+// They are buffer loads, each with a descriptor of its own 1 KB block, and
+// not global ones: while a global load into LDS is in flight the compiler
+// takes every wait for an LDS read as a wait for all of them, and the MFMAs
+// of a stage cannot start before its last fragment is there.
 template <int BM, int BN, int S, int NW>
 struct StageDMA {
   static constexpr int BLK = 16;
   static constexpr int NBA = S * BM / BLK, NBB = S * BN / BLK;
   static constexpr int NU = (NBA + NBB + NW - 1) / NW;
-  const char *src[NU];   // this lane's 16 bytes of block w + u NW, at summation byte 0
-  int dst[NU];           // the block's byte offset in a stage buffer (uniform)
-  int nu;                // blocks of this wave (uniform)
+  // a block's bytes of summation block 0 (uniform) and its place in a stage buffer
+  uint64_t src[NU];
+  int dst[NU];
+  int voff;              // this lane's 16 bytes of a block: the same in every block
 
   __device__ __forceinline__ void init(const char *__restrict__ A, const char *__restrict__ B, int64_t Mp,
                                        int64_t Np, int64_t m0, int64_t n0, int wave, int lane) {
     const int w = __builtin_amdgcn_readfirstlane(wave);   // (the compiler cannot tell it is uniform)
-    nu = 0;
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const int blk = w + u * NW;
-      int p, g, base;
-      const char *rows;
-      int64_t rows_p;
-      if (blk < NBA) {   // constant divisors on either side
-        p = blk / (BM / BLK);
-        g = blk % (BM / BLK);
-        rows = A;
-        rows_p = int64_t(p) * Mp + m0;
-        base = p * BM * 64;
-      } else {
-        const int b2 = blk - NBA < NBB ? blk - NBA : NBB - 1;
-        p = b2 / (BN / BLK);
-        g = b2 % (BN / BLK);
-        rows = B;
-        rows_p = int64_t(p) * Np + n0;
-        base = S * BM * 64 + p * BN * 64;
-      }
-      const int row = g * BLK + (lane >> 2);
-      const int c = (lane & 3) ^ ((row >> 2) & 3);
-      src[u] = rows + (rows_p + row) * 64 + c * 16;
-      dst[u] = base + g * BLK * 64;
-      nu += blk < NBA + NBB ? 1 : 0;
+      const int b0 = w + u * NW, blk = b0 < NBA + NBB ? b0 : NBA + NBB - 1;
+      const bool isA = blk < NBA;
+      const int b1 = isA ? blk : blk - NBA;
+      const int p = isA ? b1 / (BM / BLK) : b1 / (BN / BLK), g = isA ? b1 % (BM / BLK) : b1 % (BN / BLK);
+      const int64_t row = isA ? int64_t(p) * Mp + m0 : int64_t(p) * Np + n0;
+      src[u] = reinterpret_cast<uint64_t>((isA ? A : B) + (row + g * BLK) * 64);
+      dst[u] = blk * 1024;
     }
+    voff = (lane >> 2) * 64 + ((lane & 3) ^ ((lane >> 4) & 3)) * 16;
   }
 
   __device__ __forceinline__ void issue(lds_t<char> *buf, int64_t kb0) const {
 #pragma unroll
     for (int u = 0; u < NU; ++u)
-      if ((NBA + NBB) % NW == 0 || u < nu)
-        __builtin_amdgcn_global_load_lds(reinterpret_cast<const glb_t<void> *>(to_glb(src[u] + kb0)),
-                                         reinterpret_cast<lds_t<void> *>(buf + dst[u]), 16, 0, 0);
-  }
-};
-
-// The same stage loads with 32-bit lane offsets from one base (the A slices'
-// first row; B's follows dB bytes on, and a summation block of both spans
-// less than 4 GB), one per block of this wave: wave w of NW
-// takes blocks w, w + NW, ..., every wave the same number (a wave short of
-// blocks loads the last one again, the same bytes to the same place).  A
-// block's place in the stage buffer is its index x 1 KB: A's S slices of BM
-// rows, then B's S slices of BN rows, 64-byte rows.
-template <int BM, int BN, int S, int NW>
-struct StageDMA32 {
-  static constexpr int BLK = 16;
-  static constexpr int NBA = S * BM / BLK, NBB = S * BN / BLK;
-  static constexpr int NU = (NBA + NBB + NW - 1) / NW;
-  uint32_t voff[NU];
-  int w;
-
-  __device__ __forceinline__ void init(int64_t dB, int64_t Mp, int64_t Np, int64_t m0, int64_t n0, int wave,
-                                       int lane) {
-    w = __builtin_amdgcn_readfirstlane(wave);
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int b0 = w + u * NW;
-      const int blk = b0 < NBA + NBB ? b0 : NBA + NBB - 1;
-      int64_t row;   // row of the packed slices (all S of an operand stacked), relative to its base
-      int64_t base;
-      int g;
-      if (blk < NBA) {   // constant divisors on either side
-        g = blk % (BM / BLK);
-        row = int64_t(blk / (BM / BLK)) * Mp + m0;
-        base = 0;
-      } else {
-        g = (blk - NBA) % (BN / BLK);
-        row = int64_t((blk - NBA) / (BN / BLK)) * Np + n0;
-        base = dB;
-      }
-      const int r = g * BLK + (lane >> 2);
-      const int c = (lane & 3) ^ ((r >> 2) & 3);
-      voff[u] = uint32_t(base + (row + r) * 64 + c * 16);
-    }
-  }
-
-  __device__ __forceinline__ void issue(const char *__restrict__ base, lds_t<char> *buf, int64_t kb0) const {
-    const glb_t<const char> *b = to_glb(base + kb0);
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int b0 = w + u * NW;
-      const int blk = b0 < NBA + NBB ? b0 : NBA + NBB - 1;
-      __builtin_amdgcn_global_load_lds(reinterpret_cast<const glb_t<void> *>(b + voff[u]),
-                                       reinterpret_cast<lds_t<void> *>(buf + blk * 1024), 16, 0, 0);
-    }
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(src[u] + kb0), 0, 1024, 0x00020000),
+          reinterpret_cast<lds_t<void> *>(buf + dst[u]), 16, voff, 0, 0, 0);
   }
 };
 
@@ -1012,18 +951,11 @@ __global__ __launch_bounds__(WNT) void split_gemm_wide_kernel(const ST *__restri
     return buf + S * WBM * GBK + (p * WBN) * GBK + sw(row, c);
   };
   const int64_t nst = Kp / GBK;   // even: Kp is a multiple of 64
-  // (the launch checks that a summation block of the slices spans less
-  // than 4 GB)
-  const char *const base = reinterpret_cast<const char *>(As);
-  StageDMA32<WBM, WBN, S, WNT / 64> sd;
-  sd.init(reinterpret_cast<const char *>(Bs) - base, Mp, Np, m0, n0, wave, lane);
+  StageDMA<WBM, WBN, S, WNT / 64> sd;
+  sd.init(reinterpret_cast<const char *>(As), reinterpret_cast<const char *>(Bs), Mp, Np, m0, n0, wave, lane);
   const int64_t RT = slice_rows(S, Mp, Np);
-  // every wave issues the same number of loads per stage, so a wait for all
-  // but the newer stage's loads is one constant
-  constexpr int NU = StageDMA32<WBM, WBN, S, WNT / 64>::NU;
-  static_assert(NU < 64, "loads in flight per wave fit the counter");
   auto dma = [&](lds_t<ST> *buf, int64_t st) {
-    sd.issue(base, reinterpret_cast<lds_t<char> *>(buf), (st < nst ? st : nst - 1) * RT * 64);
+    sd.issue(reinterpret_cast<lds_t<char> *>(buf), (st < nst ? st : nst - 1) * RT * 64);
   };
   // fold the exact diagonal accumulators / the third one into FP64
   auto fold01_rows = [&](int i0, int i1) {
@@ -1469,8 +1401,6 @@ Status split_prepare(const Analysis &an, SplitPlan &sp, int force_tile) {
     sp.tile = (an.m >= 1024 && an.n >= 1024 && waste <= 1.1) ? 2 : 0;
     if (env && *env) sp.tile = std::atoi(env) == 2 ? 2 : 0;
     if (force_tile >= 0) sp.tile = force_tile == 2 ? 2 : 0;
-    // its loads address a summation block of the slices with 32-bit offsets
-    if (64.0 * sp.S * (double(round_up(an.m, WBM)) + double(round_up(an.n, 192))) >= 4294967296.0) sp.tile = 0;
   }
   const SplitShape &X = kSplitShapes[sp.shape];
   sp.bm = sp.tile == 2 ? WBM : X.bm;
