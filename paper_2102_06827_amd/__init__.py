@@ -352,23 +352,30 @@ class Plan:
         n = ctypes.c_size_t()
         _check(lib().comet_plan_workspace_size(self._h, ctypes.byref(n)))
         self.workspace_bytes = n.value
-        self._ws = None
+        self._ws = {}
 
     def describe(self):
         buf = ctypes.create_string_buffer(1 << 16)
         _check(lib().comet_plan_describe(self._h, buf, len(buf)))
         return json.loads(buf.value.decode())
 
-    def workspace(self, device):
-        if self.workspace_bytes and (self._ws is None or self._ws.device != device):
-            self._ws = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=device)
-        return self._ws
+    def workspace(self, device, stream=None):
+        """The plan's workspace for a stream (one each: executions on two
+        streams may overlap), None if it needs none."""
+        if not self.workspace_bytes:
+            return None
+        key = (device, _stream_handle(stream).value)
+        ws = self._ws.get(key)
+        if ws is None:
+            with torch.cuda.stream(stream):   # freed in this stream's order (None: the current one)
+                ws = self._ws[key] = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=device)
+        return ws
 
     def __call__(self, A, B, C=None, alpha=1.0, beta=0.0, workspace=None, stream=None):
         if C is None:
             C = torch.empty(self.cshape, dtype=A.dtype, device=A.device)
         _dtype_code(A, B, C)
-        ws = workspace if workspace is not None else self.workspace(A.device)
+        ws = workspace if workspace is not None else self.workspace(A.device, stream)
         wp = ctypes.c_void_p(ws.data_ptr()) if ws is not None else None
         wn = ws.numel() * ws.element_size() if ws is not None else 0
         _check(lib().comet_plan_execute(self._h, float(alpha), ctypes.c_void_p(A.data_ptr()),

@@ -259,7 +259,12 @@ constexpr double kPermuteBytesPerS = 4.5e12;
 constexpr double kPermuteLaunchS = 5.0e-6;
 constexpr size_t kTTGTMaxWorkspace = size_t(4) << 30;   // no automatic TTGT needing more
 constexpr size_t kGemvMaxWorkspace = size_t(256) << 20;   // partial sums of the matrix-vector kernel
-constexpr double kFused3MaxMNK = 0x1p31;  // above: FP32 BF16x3 through the slicer and slice-pair product
+// FP32 BF16x3 up to this many multiply-adds in the fused gather kernel, above
+// through the slicer and slice-pair product: with vector loads and an operand
+// contiguous along the summation, and otherwise (fused3_rule)
+constexpr double kFused3MaxVec = 1.2 * 0x1p30;
+constexpr double kFused3MaxElem = 0x1p26;
+constexpr double kFused3Max = 0x1p31;       // the same with batch labels or few rows or columns
 constexpr int kSkMinSteps = 8;          // fewest BK steps a stream-K share should hold
 constexpr int kSkSmallSteps = 4;        // the same for latency-bound problems (tile 1)
 constexpr double kSkBytesPerUs = 4.0e6;  // partial-sum traffic rate (HBM, both directions)
@@ -760,6 +765,36 @@ void apply_schedule(comet_plan_s *p, int cus, int forced_tile = -1) {
   }
 }
 
+// FP32 storage in BF16x3: whether to split on the fly inside the gather kernel
+// or to slice into the workspace first and run the slice-pair product, which
+// reads each operand twice more but whose tiles do more MFMA work per LDS
+// byte.  On MI355X, in us fused / sliced: with vector loads and an operand
+// contiguous along the summation 512^3 18 / 24, 1024 x 256 x 1024 33 / 37,
+// 1024^3 34 / 42, 1120^3 57 / 52, 1452^3 155 / 72; both contiguous along
+// their rows 192^3 13 / 16, 512^3 31 / 24, 1120^3 84 / 53; element loads
+// 192^3 15 / 21, 297^3 20 / 24, 1089 x 81 x 1089 55 / 45, 765^3 42 / 40,
+// 1147^3 88 / 58 and, contiguous along neither index, 512^3 39 / 29.  Fewer
+// than 64 rows or columns would be padding in the slices, a batch would be
+// sliced entry by entry, and slices beyond what an execution without
+// allocation holds would be refused there: these stay fused up to kFused3Max.
+// COMET_FUSED3=0/1 overrides.
+bool fused3_rule(const comet_plan_s *p) {
+  const Analysis &an = p->an;
+  if (an.compute != COMET_COMPUTE_SPLIT_BF16X3 || an.dtype != COMET_F32) return false;
+  const double mnk = double(an.m) * double(an.n) * double(an.k);
+  if (mnk * double(an.nb) >= kFused3Max) return false;
+  const double slices = 6.0 * (double(an.m) + double(an.n) + 512) * (double(an.k) + 64);
+  if (an.nb > 1 || std::min(an.m, an.n) < 64 || slices > COMET_NOALLOC_SCRATCH_BYTES) return true;
+  const bool vec = p->vecA_tables && p->vecB_tables &&
+                   (an.layoutA == LAYOUT_K_CONTIG || an.layoutB == LAYOUT_K_CONTIG);
+  return mnk < (vec ? kFused3MaxVec : kFused3MaxElem);
+}
+
+// The operand order that the kernels splitting on the fly read: where neither
+// index has a run of two, along the summation, as LDS holds it (297^3 20 us;
+// 23 in the order with more unit steps).
+int fused3_layout(int run_r, int run_k, int layout) { return run_r == 1 && run_k == 1 ? LAYOUT_K_CONTIG : layout; }
+
 comet_status_t build_plan(std::unique_ptr<comet_plan_s> &out, const char *spec, const int64_t *extents,
                           const int64_t *sA, const int64_t *sB, const int64_t *sC, comet_dtype_t dtype,
                           comet_compute_t compute, comet_path_t path, bool tune = true,
@@ -926,13 +961,7 @@ comet_status_t build_plan(std::unique_ptr<comet_plan_s> &out, const char *spec, 
   }
   bool split = an.compute == COMET_COMPUTE_SPLIT_BF16 || an.compute == COMET_COMPUTE_SPLIT_BF16X3 ||
                an.compute == COMET_COMPUTE_SPLIT_FP16X2 || an.compute == COMET_COMPUTE_SPLIT_INT8;
-  // FP32 storage in BF16x3: split on the fly inside the gather kernel
-  // (small products; large ones slice into the workspace first and run the
-  // slice-pair product, whose 192 x 192 tile does more MFMA work per LDS byte:
-  // on MI355X the fused kernel wins up to about 1024^3 and loses 2.4x at the
-  // 3072^3 CCSD-like contraction; COMET_FUSED3=0/1 overrides)
-  p->fused3 = an.compute == COMET_COMPUTE_SPLIT_BF16X3 && an.dtype == COMET_F32 &&
-              double(an.m) * double(an.n) * double(an.k) * double(an.nb) < kFused3MaxMNK;
+  p->fused3 = fused3_rule(p.get());
   if (an.compute == COMET_COMPUTE_SPLIT_BF16X3 && an.dtype == COMET_F32) {
     const char *env = std::getenv("COMET_FUSED3");
     if (env && *env) p->fused3 = std::atoi(env) != 0;
@@ -1099,8 +1128,8 @@ comet_status_t execute_one(const comet_plan_s *p, double alpha, const void *A, c
     g.alpha = alpha;
     g.beta = beta;
     g.dtype = 1;
-    g.layoutA = an.layoutA;
-    g.layoutB = an.layoutB;
+    g.layoutA = fused3_layout(an.runAm, an.runAk, an.layoutA);
+    g.layoutB = fused3_layout(an.runBn, an.runBk, an.layoutB);
     g.vecA = g.vecB = p->vecA_tables && p->vecB_tables && reinterpret_cast<uintptr_t>(g.A) % 16 == 0 &&
                       reinterpret_cast<uintptr_t>(g.B) % 16 == 0;
     HIP_TRY(launch_fused_bf16x3(g, s), "fused BF16x3 launch");
@@ -1256,7 +1285,7 @@ comet_status_t autotune_split(comet_plan_s *p, TuneCache &tc) {
   if (s) (void)hipStreamDestroy(s);
   if (best.tile < 0) {
     // tuning not possible: the size rule's choice
-    p->fused3 = can_fuse && double(an.m) * double(an.n) * double(an.k) * double(an.nb) < kFused3MaxMNK;
+    p->fused3 = fused3_rule(p);
     return apply(p->fused3 ? 2 : -1);
   }
   tc.store(key, best);
@@ -2394,7 +2423,10 @@ comet_status_t comet_batch_create(comet_batch_t *batch, int n, const comet_probl
       d.beta = beta;
       const bool vec = vec_tables && reinterpret_cast<uintptr_t>(d.A) % 16 == 0 &&
                        reinterpret_cast<uintptr_t>(d.B) % 16 == 0;
-      d.variant = a.layoutA * 2 + a.layoutB + (vec ? 0 : 4);
+      const bool x3 = a.compute == COMET_COMPUTE_SPLIT_BF16X3;
+      const int lA = x3 ? fused3_layout(a.runAm, a.runAk, a.layoutA) : a.layoutA;
+      const int lB = x3 ? fused3_layout(a.runBn, a.runBk, a.layoutB) : a.layoutB;
+      d.variant = lA * 2 + lB + (vec ? 0 : 4);
       d.cls = 0;
     }
   }

@@ -55,3 +55,63 @@ def test_split_block(size, block, compute, dtype, monkeypatch):
         want = full.clone()
         want[:, pad:pad + n] = (Ai.double() @ Bi.double()).to(dtype)
         assert torch.equal(dev.cpu(), want)
+
+
+# FP32 BF16x3: operand orders and sizes on either side of the line between
+# splitting in the gather kernel and slicing first
+FUSED = [
+    ("ij=ik*kj", dict(i=1024, j=1024, k=1024), True),
+    ("ij=ik*kj", dict(i=1088, j=1088, k=1096), False),
+    ("ij=ki*kj", dict(i=400, j=400, k=400), True),      # both contiguous along their rows
+    ("ij=ki*kj", dict(i=408, j=408, k=408), False),
+    ("ij=ik*kj", dict(i=405, j=405, k=405), True),      # element loads
+    ("ij=ik*kj", dict(i=407, j=409, k=407), False),
+    ("abij=acik*cbkj", dict(a=33, b=33, c=33, i=9, j=9, k=9), True),
+    ("abij=ciak*bkjc", dict(a=32, b=32, c=32, i=16, j=16, k=16), False),   # contiguous along neither index
+    ("ij=ik*jk", dict(i=63, j=3001, k=2001), True),     # few rows
+    ("ij=ik*jk", dict(i=65, j=3001, k=2001), False),
+    ("ij=ik*jk", dict(i=65, j=65, k=30001), False),     # slices of 128 MiB at most
+    ("ij=ik*jk", dict(i=65, j=65, k=40001), True),
+    ("bij=bik*bkj", dict(b=9, i=300, j=301, k=299), True),                 # batch entries
+]
+
+
+@pytest.mark.parametrize("spec,ext,fused", FUSED)
+def test_fp32_bf16x3_rule(spec, ext, fused):
+    """The path of each form, its values within the BF16x3 bar and integers
+    bit for bit, through a plan (with and without allocation) and a call."""
+    print_case("fp32 bf16x3 rule", spec, ext)
+    out, rhs = spec.split("=")
+    a, b = rhs.split("*")
+    g = torch.Generator().manual_seed(92)
+    eq = "%s,%s->%s" % (a, b, out)
+    for ints in (False, True):
+        make = (lambda t: torch.randint(-3, 4, [ext[x] for x in t], generator=g).float()) if ints else \
+               (lambda t: torch.rand([ext[x] for x in t], generator=g) - 0.5)
+        A, B = make(a), make(b)
+        ref = torch.einsum(eq, A.double(), B.double())
+        Ad, Bd = A.cuda(), B.cuda()
+        plan = comet.Plan(spec, Ad, Bd, compute="split_bf16x3")
+        assert plan.describe()["fused3"] is fused
+        C1 = plan(Ad, Bd)
+        C2 = torch.full_like(C1, float("nan"))
+        plan.execute_noalloc(Ad, Bd, C2)
+        C3 = comet.contract(spec, Ad, Bd, compute="split_bf16x3")
+        for C in (C1, C2, C3):
+            got = C.cpu().double()
+            if ints:
+                assert torch.equal(got, ref)
+            else:
+                assert (got - ref).norm() <= 1e-5 * ref.norm()
+
+
+def test_plan_workspaces_of_two_streams():
+    """Executions of one plan on two streams have a workspace each."""
+    A = torch.rand(600, 600, device="cuda", dtype=torch.float64)
+    plan = comet.Plan("ij=ik*kj", A, A, compute="split_bf16x3")
+    s = torch.cuda.Stream()
+    own = plan.workspace(A.device)
+    with torch.cuda.stream(s):
+        other = plan.workspace(A.device)
+    assert own is plan.workspace(A.device) and other is not own
+    assert plan.workspace(A.device, s) is other
