@@ -578,13 +578,13 @@ int shortk_choice(const Analysis &an, int cus, bool vecA, bool vecB, int forced_
   const int64_t T = ((an.m + 127) / 128) * ((an.n + 127) / 128);
   const char *env = std::getenv("COMET_GETT_SHORTK");
   if (env && *env) return std::atoi(env) != 0 ? int(S) : 0;
-  // Against the packed kernel's small tiles, which fill the last round
-  // better (K = 20, FP64, 2000 tiles: 65 us either way; K = 32, 8192 tiles:
-  // 250 against 281; FP32, 2684 tiles in 5.2 rounds: 70 against 59, 3456 in
-  // 6.75: 66 against 77), and which write partial segments of C past the
-  // caches as this kernel does not (K = 30, 3000 x 9000: 130 against 57).
-  const int64_t rounds = (T + S - 1) / S;
-  return T >= 4 * S && c_segments(an) && 20 * T >= 19 * rounds * S ? int(S) : 0;
+  // Against the packed kernel's 64 x 64 tiles, which fill the last round
+  // better (FP64 K = 16, 1024 tiles: 38 us against 26; K = 20, 2000: 62 / 59;
+  // K = 25, 3950: 112 / 113; K = 32, 8192: 222 / 245; FP32 K = 25, 3950: 72 /
+  // 72; K = 29, 6148: 101 / 111; K = 31, 7502: 124 / 135), and which write
+  // partial segments of C past the caches as this kernel does not (K = 30,
+  // 3000 x 9000: 130 against 57).
+  return T >= 8 * S && c_segments(an) ? int(S) : 0;
 }
 
 // The packed kernel's schedule: its tile, the tiles computed whole and the
@@ -605,15 +605,21 @@ constexpr double kPackedMore[2] = {0.585, 0.569};  // a further tile of the CU, 
 constexpr double kPackedLaunch[2] = {3.7, 4.1};    // a launch
 constexpr double kPackedFixup[2] = {4.5, 3.7};     // the fix-up launch ...
 constexpr double kPackedBytes = 5.7e6;             // ... and the partial tiles' traffic, bytes per us
-constexpr double kPackedStore[2] = {3.76e6, 3.08e6};   // output bytes (whole tiles) per us
+// output bytes (whole tiles) per us: stored past the caches in whole
+// segments, and through them
+constexpr double kPackedStore[2][2][kPackedTiles] = {
+    {{3.60e6, 4.36e6, 3.90e6, 3.55e6, 3.58e6}, {2.45e6, 3.95e6, 3.50e6, 3.15e6, 3.07e6}},
+    {{3.50e6, 3.60e6, 3.40e6, 2.75e6, 2.80e6}, {2.75e6, 2.75e6, 2.50e6, 2.25e6, 2.05e6}},
+};
 constexpr int64_t kPackedEntryK = 96;              // see packed_choice
+constexpr int64_t kPackedHalfK = 16, kPackedHalfOut = int64_t(1) << 24;   // the same
 constexpr int kPackedMinSteps = 2;                 // fewest steps a share should hold
 
 double packed_time_us(int dt, int tile, int resident, int cus, int64_t T, int64_t nk, size_t slot, int64_t whole,
-                      int64_t shares) {
+                      int64_t shares, bool segments) {
   const PackedRate &r = kPackedRate[dt][tile];
   const double per_cu = double(std::max(whole + shares, T)) / cus;
-  const double store = double(T) * double(slot) / kPackedStore[dt];
+  const double store = double(T) * double(slot) / kPackedStore[dt][segments ? 0 : 1][tile];
   double us;
   if (shares == 0) {
     const int64_t c = (T + cus - 1) / cus;
@@ -648,8 +654,13 @@ void packed_choice(comet_plan_s *p, int cus, bool gather_forced) {
   // instruction (4096 x 64^3 in FP64 65 us against 70, 500 x 96^3 33 against
   // 36; FP32 36 against 42 and 21 against 23; but 4000 x 32^3, whose entries
   // half fill their tile, 32 against 23, and 300 x 100^3 34 against 31).
-  if (!an.X.empty() && p->vecA_tables && p->vecB_tables && an.k <= kPackedEntryK && an.m > 32 && an.n > 32) return;
+  const bool vec = p->vecA_tables && p->vecB_tables;
+  if (!an.X.empty() && vec && an.k <= kPackedEntryK && an.m > 32 && an.n > 32) return;
   const int dt = an.dtype == COMET_F64 ? 0 : 1;
+  // FP32 with half a step of summation, read in vectors, and C in whole
+  // segments (K = 12, 3072 x 2304: 9.7 us against 12.2; K = 15, 3840 x 3600:
+  // 16.0 / 19.3; but K = 16, 4096 x 4096: 26.8 / 21.8)
+  if (dt == 1 && vec && an.X.empty() && an.k <= kPackedHalfK && p->pk.c_segments && an.m * an.n < kPackedHalfOut) return;
   const size_t limit = COMET_NOALLOC_SCRATCH_BYTES;
   const size_t budget = p->ws_taken > limit ? SIZE_MAX : limit - p->ws_taken;
   int ft = -1;
@@ -670,7 +681,8 @@ void packed_choice(comet_plan_s *p, int cus, bool gather_forced) {
     auto consider = [&](int64_t whole, int64_t shares) {
       const size_t ws = 2 * size_t(shares) * slot;
       if (ws > budget) return;
-      const double us = packed_time_us(dt, tile, res, int(C), T * an.nb, nk, slot, whole, shares);
+      const double us = packed_time_us(dt, tile, res, int(C), T * an.nb, nk, slot, whole, shares,
+                                    p->pk.c_segments != 0);
       if (us >= best) return;
       best = us;
       best_ws = ws;

@@ -449,16 +449,17 @@ __global__ __launch_bounds__(64 * kTiles[TILE].wgm * kTiles[TILE].wgn) void gett
 constexpr int kShortK = 32;
 
 // Where the short-summation kernel's lanes outside the output store: a
-// location per thread of a workgroup, a workgroup in 64 (all lanes storing to
-// one location queued up behind each other: K = 30 with a 3000 x 9000 output
-// took 176 us).
+// location per wave, a workgroup in 64 (all waves storing to one location
+// queue up behind each other: K = 30 with a 3000 x 9000 output took 176 us; a
+// location per lane makes partial segments of them: FP32 K = 29, 7424 x 13456
+// 133 us, 101 so).
 constexpr int kSinkGroups = 64;
 template <int NT>
 __device__ __forceinline__ double *shortk_sink();
 __device__ __align__(16) double shortk_sink_[kSinkGroups * 512];
 template <>
 __device__ __forceinline__ double *shortk_sink<512>() {
-  return shortk_sink_ + (blockIdx.x % kSinkGroups) * 512 + threadIdx.x;
+  return shortk_sink_ + (blockIdx.x % kSinkGroups) * 512 + (threadIdx.x & ~63u);
 }
 
 template <typename Tin, typename Tc, int TILE, int LA, int LB>

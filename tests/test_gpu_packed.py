@@ -184,3 +184,30 @@ def test_batch_of_odd_problems(cls, dtype, monkeypatch):
         want = [oracle.contract(s, A, B, C, alpha=al, beta=be) for (s, A, B, _, al, be), C in zip(host, want)]
         for (s, *_), x, ref in zip(host, dev, want):
             assert np.array_equal(to_np(x["C"]), ref), s
+
+
+@pytest.mark.parametrize("m,n,k,dtype,kernel", [
+    (3072, 2304, 12, "f32", "gather"),      # half a step of summation, C in whole segments
+    (3072, 2305, 12, "f32", "packed"),      # ... and not
+    (3072, 2304, 17, "f32", "packed"),
+    (4096, 4096, 16, "f32", "packed"),      # 2^24 outputs
+    (3072, 2304, 12, "f64", "packed"),
+    (5888, 5632, 16, "f64", "packed"),      # 2024 tiles of 128 x 128: less than 8 rounds of a workgroup per CU
+    (5800, 5888, 16, "f64", "shortk"),      # 2116
+    (8192, 8400, 32, "f32", "shortk"),      # 4224
+    (8000, 8192, 32, "f32", "packed"),      # 4032 tiles, two workgroups a CU
+])
+def test_short_summations(m, n, k, dtype, kernel):
+    """Which kernel takes a short summation, and its integers bit for bit."""
+    print_case("short summations", m, n, k, dtype)
+    g = torch.Generator().manual_seed(93)
+    A = torch.randint(-3, 4, (m, k), generator=g).to(DT[dtype])
+    B = torch.randint(-3, 4, (n, k), generator=g).to(DT[dtype])
+    C = torch.full((m, n), float("nan"), dtype=DT[dtype], device="cuda")
+    plan = comet.Plan("mn=mk*nk", A.cuda(), B.cuda(), C)
+    d = plan.describe()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if cus == 256:
+        assert ("shortk" if d["shortk"] else "packed" if d["packed"] else "gather") == kernel, d
+    plan(A.cuda(), B.cuda(), C)
+    assert torch.equal(C.cpu(), A @ B.T)
