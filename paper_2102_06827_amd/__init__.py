@@ -166,9 +166,11 @@ def extents_of(spec, A_shape, B_shape):
 
 
 def _stream_handle(stream):
+    """The stream's handle (an int); None: the current stream's, asked for
+    without a Stream object (0.4 us instead of 2.9)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _dtype_code(*ts):
@@ -183,26 +185,34 @@ def _dtype_code(*ts):
     return _DTYPE[dt]
 
 
-# Marshalled call arguments of comet_contract by (spec, shapes, strides):
-# repeated calls on same-shaped tensors skip the label bookkeeping.
+# Marshalled call arguments by (spec, shapes, strides): repeated calls on
+# same-shaped tensors skip the label bookkeeping.  The arrays are only read.
 _ARGS_CACHE = {}
 _ARGS_CACHE_MAX = 256
 
 
+def _remember(key, val):
+    if len(_ARGS_CACHE) >= _ARGS_CACHE_MAX:
+        _ARGS_CACHE.clear()
+    _ARGS_CACHE[key] = val
+    return val
+
+
+def _dense(shape):
+    """The strides of torch.empty(shape)."""
+    return torch.empty(shape, device="meta").stride()
+
+
 def _contract_args(spec, A, B, C):
-    key = (spec, tuple(A.shape), A.stride(), tuple(B.shape), B.stride(), None if C is None else (tuple(C.shape), C.stride()))
+    key = (spec, A.shape, A.stride(), B.shape, B.stride(), None if C is None else (C.shape, C.stride()))
     hit = _ARGS_CACHE.get(key)
     if hit is not None:
         return hit
     ext, cshape = extents_of(spec, A.shape, B.shape)
     if C is not None and tuple(C.shape) != cshape:
         raise ValueError("C shape %s != %s" % (tuple(C.shape), cshape))
-    val = (spec.encode(), _i64(ext), cshape, _i64(A.stride()), _i64(B.stride()),
-           None if C is None else _i64(C.stride()))
-    if len(_ARGS_CACHE) >= _ARGS_CACHE_MAX:
-        _ARGS_CACHE.clear()
-    _ARGS_CACHE[key] = val
-    return val
+    return _remember(key, (spec.encode(), _i64(ext), cshape, _i64(A.stride()), _i64(B.stride()),
+                           _i64(_dense(cshape) if C is None else C.stride())))
 
 
 def contract(spec, A, B, C=None, alpha=1.0, beta=0.0, compute="default", stream=None):
@@ -215,30 +225,32 @@ def contract(spec, A, B, C=None, alpha=1.0, beta=0.0, compute="default", stream=
         if beta != 0.0:
             raise ValueError("beta != 0 needs C")
         C = torch.empty(cshape, dtype=A.dtype, device=A.device)
-        sc = _i64(C.stride())
     dt = _dtype_code(A, B, C)
-    rc = lib().comet_contract(spec_b, ext, dt, COMPUTE[compute], float(alpha),
-                              ctypes.c_void_p(A.data_ptr()), sa,
-                              ctypes.c_void_p(B.data_ptr()), sb, float(beta),
-                              ctypes.c_void_p(C.data_ptr()), sc, _stream_handle(stream))
+    rc = lib().comet_contract(spec_b, ext, dt, COMPUTE[compute], float(alpha), A.data_ptr(), sa, B.data_ptr(), sb,
+                              float(beta), C.data_ptr(), sc, _stream_handle(stream))
     _check(rc)
     return C
 
 
 def permute(spec, x, out=None, alpha=1.0, beta=0.0, stream=None):
     """out = alpha * x with labels permuted ("ji=ij") + beta * out."""
-    s = "".join(spec.split())
-    lo, li = s.split("=")
-    if len(li) != x.dim():
-        raise ValueError("rank mismatch")
-    ext_in = dict(zip(li, x.shape))
-    ext = [int(ext_in[ch]) for ch in lo]
+    key = ("permute", spec, x.shape, x.stride(), None if out is None else out.stride())
+    args = _ARGS_CACHE.get(key)
+    if args is None:
+        s = "".join(spec.split())
+        lo, li = s.split("=")
+        if len(li) != x.dim():
+            raise ValueError("rank mismatch")
+        ext_in = dict(zip(li, x.shape))
+        ext = tuple(int(ext_in[ch]) for ch in lo)
+        args = _remember(key, (s.encode(), _i64(ext), ext, _i64(x.stride()),
+                               _i64(_dense(ext) if out is None else out.stride())))
+    spec_b, ext_c, ext, si, so = args
     if out is None:
-        out = torch.empty(tuple(ext), dtype=x.dtype, device=x.device)
+        out = torch.empty(ext, dtype=x.dtype, device=x.device)
     dt = _dtype_code(x, out)
-    rc = lib().comet_permute(s.encode(), _i64(ext), dt, float(alpha), ctypes.c_void_p(x.data_ptr()),
-                             _i64(x.stride()), float(beta), ctypes.c_void_p(out.data_ptr()),
-                             _i64(out.stride()), _stream_handle(stream))
+    rc = lib().comet_permute(spec_b, ext_c, dt, float(alpha), x.data_ptr(), si, float(beta), out.data_ptr(), so,
+                             _stream_handle(stream))
     _check(rc)
     return out
 
@@ -273,26 +285,33 @@ def chain_plan(spec, extents):
 def contract_chain(spec, tensors, C=None, alpha=1.0, beta=0.0, compute="default", stream=None):
     """C = alpha * (A1 * ... * An) + beta * C for spec "C=A1*...*An", in the
     order with the fewest operations (intermediates held by the library)."""
-    out, ops = _chain_parts(spec)
-    if len(ops) != len(tensors):
-        raise ValueError("spec has %d operands, %d tensors given" % (len(ops), len(tensors)))
-    ext = {}
-    for labels, t in zip(ops, tensors):
-        if len(labels) != t.dim():
-            raise ValueError("rank mismatch for operand " + labels)
-        for ch, e in zip(labels, t.shape):
-            if ext.setdefault(ch, int(e)) != int(e):
-                raise ValueError("extent mismatch for label " + ch)
+    key = ("chain", spec, tuple((t.shape, t.stride()) for t in tensors), None if C is None else C.stride())
+    args = _ARGS_CACHE.get(key)
+    if args is None:
+        out, ops = _chain_parts(spec)
+        if len(ops) != len(tensors):
+            raise ValueError("spec has %d operands, %d tensors given" % (len(ops), len(tensors)))
+        ext = {}
+        for labels, t in zip(ops, tensors):
+            if len(labels) != t.dim():
+                raise ValueError("rank mismatch for operand " + labels)
+            for ch, e in zip(labels, t.shape):
+                if ext.setdefault(ch, int(e)) != int(e):
+                    raise ValueError("extent mismatch for label " + ch)
+        cshape = tuple(ext[ch] for ch in out)
+        strs = [_i64(t.stride()) for t in tensors]   # kept with the array that points to them
+        sarr = (ctypes.POINTER(ctypes.c_int64) * len(strs))(*[ctypes.cast(x, ctypes.POINTER(ctypes.c_int64))
+                                                              for x in strs])
+        args = _remember(key, (spec.encode(), _i64([ext[ch] for ch in chain_labels(spec)]), cshape, sarr,
+                               _i64(_dense(cshape) if C is None else C.stride()), strs))
+    spec_b, ext_c, cshape, sarr, sc, _ = args
     if C is None:
-        C = torch.empty(tuple(ext[ch] for ch in out), dtype=tensors[0].dtype, device=tensors[0].device)
-    dt = _dtype_code(*(list(tensors) + [C]))
+        C = torch.empty(cshape, dtype=tensors[0].dtype, device=tensors[0].device)
+    dt = _dtype_code(*tensors, C)
     n = len(tensors)
     ptrs = (ctypes.c_void_p * n)(*[t.data_ptr() for t in tensors])
-    strs = [_i64(t.stride()) for t in tensors]
-    sarr = (ctypes.POINTER(ctypes.c_int64) * n)(*[ctypes.cast(x, ctypes.POINTER(ctypes.c_int64)) for x in strs])
-    rc = lib().comet_contract_chain(spec.encode(), _i64([ext[ch] for ch in chain_labels(spec)]), dt,
-                                    COMPUTE[compute], float(alpha), n, ptrs, sarr, float(beta),
-                                    ctypes.c_void_p(C.data_ptr()), _i64(C.stride()), _stream_handle(stream))
+    rc = lib().comet_contract_chain(spec_b, ext_c, dt, COMPUTE[compute], float(alpha), n, ptrs, sarr, float(beta),
+                                    C.data_ptr(), sc, _stream_handle(stream))
     _check(rc)
     return C
 
@@ -364,7 +383,7 @@ class Plan:
         streams may overlap), None if it needs none."""
         if not self.workspace_bytes:
             return None
-        key = (device, _stream_handle(stream).value)
+        key = (device, _stream_handle(stream))
         ws = self._ws.get(key)
         if ws is None:
             with torch.cuda.stream(stream):   # freed in this stream's order (None: the current one)
@@ -376,11 +395,10 @@ class Plan:
             C = torch.empty(self.cshape, dtype=A.dtype, device=A.device)
         _dtype_code(A, B, C)
         ws = workspace if workspace is not None else self.workspace(A.device, stream)
-        wp = ctypes.c_void_p(ws.data_ptr()) if ws is not None else None
+        wp = ws.data_ptr() if ws is not None else None
         wn = ws.numel() * ws.element_size() if ws is not None else 0
-        _check(lib().comet_plan_execute(self._h, float(alpha), ctypes.c_void_p(A.data_ptr()),
-                                        ctypes.c_void_p(B.data_ptr()), float(beta),
-                                        ctypes.c_void_p(C.data_ptr()), wp, wn, _stream_handle(stream)))
+        _check(lib().comet_plan_execute(self._h, float(alpha), A.data_ptr(), B.data_ptr(), float(beta), C.data_ptr(),
+                                        wp, wn, _stream_handle(stream)))
         return C
 
     def execute_noalloc(self, A, B, C, alpha=1.0, beta=0.0, stream=None):

@@ -12,9 +12,12 @@ library call as the forward.
 """
 from __future__ import annotations
 
+import functools
+
 import torch
 
 
+@functools.lru_cache(maxsize=256)
 def grad_specs(spec):
     s = "".join(spec.split())
     c, rhs = s.split("=")

@@ -12,6 +12,7 @@
 #include <mutex>
 #include <string>
 #include <vector>
+#include <unistd.h>
 
 #include "chain.hpp"
 #include "comet.h"
@@ -1892,7 +1893,9 @@ comet_status_t batch_tune_classes(const std::vector<Analysis> &an, const std::ve
 // after the last enqueued use, and a later user waits for it (on the device)
 // before touching the buffer, so a buffer whose stream handle is reused by a
 // new stream, or which is grown, is never overwritten or freed under kernels
-// still in flight.
+// still in flight.  The null stream's handle is never another stream's, and
+// its own order is enough: its buffer goes without the event (a record and a
+// wait cost a call of 5 us another 9).
 struct DeviceWorkspace {
   void *ptr = nullptr;
   size_t bytes = 0;
@@ -1903,23 +1906,26 @@ typedef std::pair<int, hipStream_t> WsKey;
 // Make `w` at least `bytes` large and usable by stream s; call with the
 // lock that guards w held, and call ws_release after enqueuing the work.
 comet_status_t ws_acquire(DeviceWorkspace &w, size_t bytes, hipStream_t s) {
-  if (!w.done) HIP_TRY(hipEventCreateWithFlags(&w.done, hipEventDisableTiming), "hipEventCreate(workspace)");
+  if (s && !w.done) HIP_TRY(hipEventCreateWithFlags(&w.done, hipEventDisableTiming), "hipEventCreate(workspace)");
   if (bytes > w.bytes) {
     // grow: the old buffer is freed only after its last use has completed
-    HIP_TRY(hipEventSynchronize(w.done), "hipEventSynchronize(workspace)");
+    if (s)
+      HIP_TRY(hipEventSynchronize(w.done), "hipEventSynchronize(workspace)");
+    else if (w.ptr)
+      HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize(workspace)");
     if (w.ptr) HIP_TRY(hipFree(w.ptr), "hipFree(workspace)");
     w.ptr = nullptr;
     w.bytes = 0;
     HIP_TRY(hipMalloc(&w.ptr, bytes), "hipMalloc(workspace)");
     w.bytes = bytes;
-  } else {
+  } else if (s) {
     HIP_TRY(hipStreamWaitEvent(s, w.done, 0), "hipStreamWaitEvent(workspace)");
   }
   return COMET_OK;
 }
 
 comet_status_t ws_release(DeviceWorkspace &w, hipStream_t s) {
-  HIP_TRY(hipEventRecord(w.done, s), "hipEventRecord(workspace)");
+  if (s) HIP_TRY(hipEventRecord(w.done, s), "hipEventRecord(workspace)");
   return COMET_OK;
 }
 // Plans of comet_contract, per device.  Each holds device tables, so the
@@ -1931,30 +1937,24 @@ std::map<WsKey, DeviceWorkspace> g_ws;
 
 std::string cache_key(const char *spec, const int64_t *ext, size_t nlab, const int64_t *sA, size_t ra,
                       const int64_t *sB, size_t rb, const int64_t *sC, size_t rc, int dtype, int compute, int dev) {
-  std::string k(spec);
+  std::string k;   // lengths before the parts, in fixed-width numbers
+  const size_t ns = std::strlen(spec);
+  k.reserve(ns + 8 * (nlab + ra + rb + rc + 12));
+  auto raw = [&](int64_t v) { k.append(reinterpret_cast<const char *>(&v), sizeof v); };
+  raw(int64_t(ns));
+  k.append(spec, ns);
   auto add = [&](const int64_t *v, size_t n) {
-    k += "|";
-    if (!v) {
-      k += "-";
-      return;
-    }
-    for (size_t i = 0; i < n; ++i) k += std::to_string(v[i]) + ",";
+    raw(v ? int64_t(n) : -1);
+    if (v) k.append(reinterpret_cast<const char *>(v), n * sizeof(int64_t));
   };
   add(ext, nlab);
   add(sA, ra);
   add(sB, rb);
   add(sC, rc);
-  k += "|" + std::to_string(dtype) + "|" + std::to_string(compute) + "|" + std::to_string(dev) + "|" +
-       std::to_string(g_split_slices) + "|" + std::to_string(g_int8_slices);
-  // every planner override in the environment
-  for (const char *name : {"COMET_FORCE_PATH", "COMET_TTGT_ORDER", "COMET_GETT_TILE", "COMET_GETT_SK",
-                           "COMET_GETT_PERSIST", "COMET_GETT_SHORTK", "COMET_GETT_EVEN", "COMET_SPLIT_TILE", "COMET_FUSED3",
-                           "COMET_PACKED"}) {
-    const char *v = std::getenv(name);
-    k += "|";
-    if (v) k += v;
-  }
-  k += "|t" + std::to_string(tune_cache().mode());
+  for (const int v : {dtype, compute, dev, g_split_slices, g_int8_slices, tune_cache().mode()}) raw(v);
+  // every planner override in the environment, in one pass over it
+  for (char **e = environ; e && *e; ++e)
+    if (std::strncmp(*e, "COMET_", 6) == 0) k.append(*e).push_back('\0');
   return k;
 }
 
