@@ -17,6 +17,7 @@
 #include "chain.hpp"
 #include "comet.h"
 #include "kernels.hpp"
+#include "permute_shape.hpp"
 #include "plan.hpp"
 #include "split.hpp"
 #include "tune.hpp"
@@ -258,6 +259,8 @@ constexpr double kVecGemmFlopsF32 = 100.0e12;
 constexpr double kDenseElemGemmFlops = 45.0e12;
 constexpr double kPermuteBytesPerS = 4.5e12;
 constexpr double kPermuteLaunchS = 5.0e-6;
+constexpr double kStoreBytesPerS = 4.0e12;
+constexpr double kOneCopySavingS = 12.5e-6;   // estimated, where one copied operand starts to pay
 constexpr size_t kTTGTMaxWorkspace = size_t(4) << 30;   // no automatic TTGT needing more
 constexpr size_t kGemvMaxWorkspace = size_t(256) << 20;   // partial sums of the matrix-vector kernel
 // FP32 BF16x3 up to this many multiply-adds in the fused gather kernel, above
@@ -282,12 +285,56 @@ bool packed_reads(const Analysis &an) {
          unit_steps(an.layoutB == LAYOUT_MN_CONTIG ? an.offBn : an.offBk) >= 0.5;
 }
 
+// The copies of one operand after which the packed kernel may read both in
+// runs: its own labels of C in C's order and the summation labels in the
+// other operand's, in either order; the other operand and C are read and
+// written in place.  The fastest copy by the permute model first, among equals
+// in the order of the products after them (FP64 3072^3 829, 850, 835 and 838
+// us, 1725^3 179, 177, 176 and 185; FP32 2240^3 195, 197, 203 and 203).
+std::vector<TTGTChoice> one_copy_choices(const Analysis &an) {
+  std::vector<TTGTChoice> out;
+  auto ext_of = [&](char ch) {
+    return an.extents[std::find(an.labels.begin(), an.labels.end(), ch) - an.labels.begin()];
+  };
+  for (int i = 0; i < 4; ++i) {
+    const bool copy_b = i < 2;
+    const std::string &x = copy_b ? an.spec_b : an.spec_a, &y = copy_b ? an.spec_a : an.spec_b;
+    const std::vector<int64_t> &sx = copy_b ? an.strB : an.strA;
+    std::string own, sum;
+    for (char ch : an.spec_c)
+      if (x.find(ch) != std::string::npos) own += ch;
+    for (char ch : y)
+      if (an.spec_c.find(ch) == std::string::npos) sum += ch;
+    const std::string order = i == 0 || i == 3 ? own + sum : sum + own;
+    if (order.size() != x.size()) continue;
+    std::vector<int64_t> e, si;
+    for (char ch : order) {
+      e.push_back(ext_of(ch));
+      si.push_back(sx[x.find(ch)]);
+    }
+    const std::vector<int64_t> so = dense_strides(e);
+    TTGTChoice c;
+    c.a_order = copy_b ? an.spec_a : order;
+    c.b_order = copy_b ? order : an.spec_b;
+    c.c_order = an.spec_c;
+    c.a_copy = !copy_b;
+    c.b_copy = copy_b;
+    c.c_copy = false;
+    c.model_us = (1.0 + 0.02 * i) * permute_time_us(permute_shape(int(e.size()), e.data(), si.data(), so.data(), true),
+                                                    int(elem_size(an.dtype)), false);
+    out.push_back(c);
+  }
+  std::stable_sort(out.begin(), out.end(),
+                   [](const TTGTChoice &p, const TTGTChoice &q) { return p.model_us < q.model_us; });
+  return out;
+}
+
 // Estimated saving (seconds, may be negative) of TTGT plan `tt` over the
 // element-load gather of the same contraction `an`: the GEMM time saved
 // minus the permutes' traffic and launches.
 double ttgt_saving_s(const Analysis &an, const comet_plan_s &tt) {
   const double flops = 2.0 * double(an.m) * double(an.n) * double(an.k);
-  const bool vec_reads = tt.gemm && tt.gemm->vecA_tables && tt.gemm->vecB_tables;
+  const bool vec_reads = tt.gemm && ((tt.gemm->vecA_tables && tt.gemm->vecB_tables) || packed_reads(tt.gemm->an));
   const double vec = !vec_reads ? kDenseElemGemmFlops
                      : an.compute == COMET_COMPUTE_F64 ? kVecGemmFlopsF64 : kVecGemmFlopsF32;
   const TTGTChoice &c = tt.an.ttgt;
@@ -680,7 +727,7 @@ void packed_choice(comet_plan_s *p, int cus, bool gather_forced) {
     if (res <= 0 || T > INT32_MAX / 2 || T * an.nb > (int64_t(1) << 40)) continue;
     const int64_t C = std::max(cus, 1), S = C * res;
     auto consider = [&](int64_t whole, int64_t shares) {
-      const size_t ws = 2 * size_t(shares) * slot;
+      const size_t ws = size_t(shares + std::min(shares, T - whole)) * slot;
       if (ws > budget) return;
       const double us = packed_time_us(dt, tile, res, int(C), T * an.nb, nk, slot, whole, shares,
                                     p->pk.c_segments != 0);
@@ -955,9 +1002,26 @@ comet_status_t build_plan(std::unique_ptr<comet_plan_s> &out, const char *spec, 
   if (path == COMET_PATH_AUTO && native && !tuning && !gather_forced && an.path == COMET_PATH_GETT &&
       an.X.empty() && !an.empty_out && !an.empty_sum && !(p->vecA_tables && p->vecB_tables) &&
       !packed_reads(an)) {
-    std::unique_ptr<comet_plan_s> tt;
-    if (build_plan(tt, spec, extents, sA, sB, sC, dtype, compute, COMET_PATH_TTGT, false) == COMET_OK && tt->gemm &&
-        tt->ws_bytes <= kTTGTMaxWorkspace && ttgt_saving_s(an, *tt) > 0.0) {
+    std::unique_ptr<comet_plan_s> tt, one;
+    const bool ttgt = build_plan(tt, spec, extents, sA, sB, sC, dtype, compute, COMET_PATH_TTGT, false) == COMET_OK &&
+                      tt->gemm && tt->ws_bytes <= kTTGTMaxWorkspace && ttgt_saving_s(an, *tt) > 0.0;
+    // One copied operand and the packed kernel in place of three permutes
+    // (FP64 1200^3 99 -> 80 us, 2240^3 421 -> 374; FP32 640^3 28 -> 18, 2240^3
+    // 228 -> 206), and in place of the element loads from smaller sizes on
+    // (FP64 957^3 111 -> 52, 676^3 32 -> 33; FP32 640^3 22 -> 18).  A copy
+    // beyond what an execution without allocation holds takes the place of
+    // TTGT's only; a product that its output's stores bound gains nothing.
+    const double stores = double(elem_size(an.dtype)) * double(an.m) * double(an.n) / kStoreBytesPerS;
+    if (packed_can(an) && 2.0 * double(an.m) * double(an.n) * double(an.k) / kElemLoadFlops > stores)
+      for (const TTGTChoice &c : one_copy_choices(an)) {
+        if (build_plan(one, spec, extents, sA, sB, sC, dtype, compute, COMET_PATH_TTGT, false, &c) != COMET_OK ||
+            !one->gemm || !packed_reads(one->gemm->an) || ttgt_saving_s(an, *one) <= kOneCopySavingS ||
+            (one->ws_bytes > COMET_NOALLOC_SCRATCH_BYTES && !(ttgt && one->ws_bytes <= tt->ws_bytes)))
+          continue;
+        out = std::move(one);
+        return COMET_OK;
+      }
+    if (ttgt) {
       out = std::move(tt);
       return COMET_OK;
     }

@@ -88,6 +88,14 @@ template <typename T, int TILE, int LA, int LB>
 using PackedKernel = PackedCore<T, packed_tile<T>(TILE).bm, packed_tile<T>(TILE).bn, packed_tile<T>(TILE).bk,
                                 packed_tile<T>(TILE).wgm, packed_tile<T>(TILE).wgn, LA, LB>;
 
+// The workspace slot of share s's piece of shared tile t.  Along the steps
+// each piece has a larger s or a larger t than the one before, so s + t
+// tells them apart; where tiles are more than the shares, each of which splits
+// two tiles at most, its first or its last.
+__device__ __forceinline__ int64_t piece_slot(int s, int t, bool begun_here, int tiles, int shares) {
+  return tiles <= shares ? int64_t(s) + t : 2 * int64_t(s) + (begun_here ? 0 : 1);
+}
+
 // first step of share s of S over I steps
 __device__ __forceinline__ int64_t share_begin(int64_t I, int S, int s) { return I * s / S; }
 
@@ -141,7 +149,8 @@ packed_kernel(PackedLaunch g) {
     } else {
       constexpr int64_t kSlot = int64_t(WT::FM) * WT::FN * WT::NT;   // 4-vectors per slot
       gett_store_partial<T, P::BM, P::BN, P::WGM, P::WGN>(
-          w, static_cast<typename WT::acc_t *>(g.ws) + (2 * int64_t(share) + (tt == first ? 0 : 1)) * kSlot);
+          w, static_cast<typename WT::acc_t *>(g.ws) +
+                 piece_slot(share, tt, tt == first, g.tilesM * g.tilesN - g.whole, g.shares) * kSlot);
     }
     it += s1 - s0;
   }
@@ -168,8 +177,9 @@ __global__ __launch_bounds__(64 * packed_tile<T>(TILE).wgm * packed_tile<T>(TILE
   constexpr int64_t kSlot = int64_t(WT::FM) * WT::FN * WT::NT;
   const glb_t<const acc_t> *const ws = to_glb(static_cast<const acc_t *>(g.ws)) + int64_t(f) * WT::NT + threadIdx.x;
   // only the first share may have begun in an earlier tile
-  acc_t v = ws[(2 * int64_t(lo) + (share_begin(I, g.shares, lo) >= x0 ? 0 : 1)) * kSlot];
-  for (int s = lo + 1; s <= hi; ++s) v = v + ws[2 * int64_t(s) * kSlot];
+  const int tiles = g.tilesM * g.tilesN - g.whole;
+  acc_t v = ws[piece_slot(lo, tt, share_begin(I, g.shares, lo) >= x0, tiles, g.shares) * kSlot];
+  for (int s = lo + 1; s <= hi; ++s) v = v + ws[piece_slot(s, tt, true, tiles, g.shares) * kSlot];
   int tm, tn;
   group_coords(g.whole + tt, g.tilesM, g.tilesN, &tm, &tn);
   gett_store_fragment<T, T, P::BM, P::BN, P::WGM, P::WGN, STREAM>(v, f / WT::FN, f % WT::FN, static_cast<T *>(g.C),

@@ -211,3 +211,30 @@ def test_short_summations(m, n, k, dtype, kernel):
         assert ("shortk" if d["shortk"] else "packed" if d["packed"] else "gather") == kernel, d
     plan(A.cuda(), B.cuda(), C)
     assert torch.equal(C.cpu(), A @ B.T)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("spec,ext", [
+    ("abij=ciak*bkjc", dict(a=60, b=61, c=59, i=16, j=17, k=16)),
+    ("abij=icak*kbjc", dict(a=60, b=30, c=33, i=18, j=21, k=20)),      # B the larger copy
+    ("ijab=bkjc*ciak", dict(a=33, b=60, c=35, i=21, j=18, k=19)),      # C transposed, A copied
+    ("jbia=ciak*bkjc", dict(a=45, b=25, c=31, i=16, j=33, k=29)),
+])
+def test_one_copied_operand(spec, ext, dtype):
+    """Unit strides on different summation labels: one operand is copied, the
+    other and C are used in place, strided ones too; integers bit for bit, with
+    beta, and through the call without a plan."""
+    print_case("one copied operand", spec, dtype)
+    A, B, C0 = inputs(spec, ext, 9701, kind="integer", beta=True)
+    Ad, Bd, Cd = (torch_dev(x, DT[dtype]) for x in (A, B, C0))
+    want = oracle.contract(spec, A, B, C0, alpha=2.0, beta=-1.0)
+    for strided in (False, True):
+        if strided:   # every other plane of a larger tensor
+            Ad, Bd, Cd = (torch.stack([x, torch.full_like(x, float("nan"))], 1)[:, 0] for x in (Ad, Bd, Cd))
+        plan = comet.Plan(spec, Ad, Bd, Cd)
+        d = plan.describe()
+        assert d["path"] == "ttgt" and [d["ttgt"][x] for x in ("copyA", "copyB", "copyC")].count(True) == 1, d["ttgt"]
+        out = Cd if strided else Cd.clone()
+        plan(Ad, Bd, out, alpha=2.0, beta=-1.0)
+        assert np.array_equal(to_np(out), want)
+        assert np.array_equal(to_np(comet.contract(spec, Ad, Bd)), oracle.contract(spec, A, B))

@@ -42,3 +42,27 @@ def test_shares_cover_the_steps_and_the_fixup_finds_them(tiles, steps):
             assert tile not in whole
             read = [2 * lo + (0 if begin(I, S, lo) >= x0 else 1)] + [2 * s for s in range(lo + 1, hi + 1)]
             assert [slots[r] for r in read] == [(tile, s) for s in range(lo, hi + 1)]
+
+
+@pytest.mark.parametrize("tiles,steps", [(1, 2), (2, 7), (5, 12), (17, 4), (64, 9), (100, 23)])
+def test_slots_of_at_most_as_many_tiles_as_shares(tiles, steps):
+    """With the slot s + t every piece has its own, below shares + tiles, and a
+    tile's pieces lie next to each other in share order."""
+    I = tiles * steps
+    for S in sorted({tiles, tiles + 1, 2 * tiles - 1, 3 * tiles, I - 1, I} & set(range(tiles, I + 1))):
+        slots = {}
+        for s in range(S):
+            it, end = begin(I, S, s), begin(I, S, s + 1)
+            while it < end:
+                t = it // steps
+                n = min(end, (t + 1) * steps) - it
+                if n < steps:
+                    assert s + t not in slots and s + t < S + tiles
+                    slots[s + t] = (s, t, n)
+                it += n
+        for t in range(tiles):
+            x0, x1 = t * steps, (t + 1) * steps - 1
+            lo, hi = ((x0 + 1) * S - 1) // I, ((x1 + 1) * S - 1) // I
+            if lo < hi:
+                assert [slots[s + t][:2] for s in range(lo, hi + 1)] == [(s, t) for s in range(lo, hi + 1)]
+                assert sum(slots[s + t][2] for s in range(lo, hi + 1)) == steps
