@@ -329,15 +329,14 @@ std::vector<TTGTChoice> one_copy_choices(const Analysis &an) {
   return out;
 }
 
-// Estimated saving (seconds, may be negative) of TTGT plan `tt` over the
-// element-load gather of the same contraction `an`: the GEMM time saved
-// minus the permutes' traffic and launches.
-double ttgt_saving_s(const Analysis &an, const comet_plan_s &tt) {
+// Estimated saving (seconds, may be negative) of flattening `c` over the
+// element-load gather of the contraction `an`: the GEMM time saved (`runs`: its
+// operands are read in vectors or in runs) minus the permutes' traffic and
+// launches.
+double ttgt_saving_s(const Analysis &an, const TTGTChoice &c, bool runs) {
   const double flops = 2.0 * double(an.m) * double(an.n) * double(an.k);
-  const bool vec_reads = tt.gemm && ((tt.gemm->vecA_tables && tt.gemm->vecB_tables) || packed_reads(tt.gemm->an));
-  const double vec = !vec_reads ? kDenseElemGemmFlops
-                     : an.compute == COMET_COMPUTE_F64 ? kVecGemmFlopsF64 : kVecGemmFlopsF32;
-  const TTGTChoice &c = tt.an.ttgt;
+  const double rate = !runs ? kDenseElemGemmFlops
+                      : an.compute == COMET_COMPUTE_F64 ? kVecGemmFlopsF64 : kVecGemmFlopsF32;
   const double es = double(elem_size(an.dtype));
   auto count = [&](const std::string &labels) {
     double n = 1.0;
@@ -350,7 +349,7 @@ double ttgt_saving_s(const Analysis &an, const comet_plan_s &tt) {
   if (c.a_copy) bytes += 2.0 * es * count(an.spec_a), ++launches;
   if (c.b_copy) bytes += 2.0 * es * count(an.spec_b), ++launches;
   if (c.c_copy) bytes += 3.0 * es * count(an.spec_c), ++launches;   // GEMM write, then read + write
-  return flops / kElemLoadFlops - flops / vec - bytes / kPermuteBytesPerS - launches * kPermuteLaunchS;
+  return flops / kElemLoadFlops - flops / rate - bytes / kPermuteBytesPerS - launches * kPermuteLaunchS;
 }
 
 int tile_resident(const Analysis &an, int tile, bool vecA, bool vecB) {
@@ -1003,24 +1002,35 @@ comet_status_t build_plan(std::unique_ptr<comet_plan_s> &out, const char *spec, 
       an.X.empty() && !an.empty_out && !an.empty_sum && !(p->vecA_tables && p->vecB_tables) &&
       !packed_reads(an)) {
     std::unique_ptr<comet_plan_s> tt, one;
-    const bool ttgt = build_plan(tt, spec, extents, sA, sB, sC, dtype, compute, COMET_PATH_TTGT, false) == COMET_OK &&
-                      tt->gemm && tt->ws_bytes <= kTTGTMaxWorkspace && ttgt_saving_s(an, *tt) > 0.0;
+    bool ttgt = false;
+    auto try_ttgt = [&]() {
+      if (tt) return;
+      ttgt = build_plan(tt, spec, extents, sA, sB, sC, dtype, compute, COMET_PATH_TTGT, false) == COMET_OK && tt->gemm &&
+             tt->ws_bytes <= kTTGTMaxWorkspace &&
+             ttgt_saving_s(an, tt->an.ttgt, (tt->gemm->vecA_tables && tt->gemm->vecB_tables) ||
+                                                packed_reads(tt->gemm->an)) > 0.0;
+    };
     // One copied operand and the packed kernel in place of three permutes
-    // (FP64 1200^3 99 -> 80 us, 2240^3 421 -> 374; FP32 640^3 28 -> 18, 2240^3
-    // 228 -> 206), and in place of the element loads from smaller sizes on
+    // (FP64 1200^3 99 -> 84 us, 2240^3 421 -> 395; FP32 640^3 28 -> 18, 2240^3
+    // 231 -> 211), and in place of the element loads from smaller sizes on
     // (FP64 957^3 111 -> 52, 676^3 32 -> 33; FP32 640^3 22 -> 18).  A copy
     // beyond what an execution without allocation holds takes the place of
     // TTGT's only; a product that its output's stores bound gains nothing.
     const double stores = double(elem_size(an.dtype)) * double(an.m) * double(an.n) / kStoreBytesPerS;
     if (packed_can(an) && 2.0 * double(an.m) * double(an.n) * double(an.k) / kElemLoadFlops > stores)
       for (const TTGTChoice &c : one_copy_choices(an)) {
-        if (build_plan(one, spec, extents, sA, sB, sC, dtype, compute, COMET_PATH_TTGT, false, &c) != COMET_OK ||
-            !one->gemm || !packed_reads(one->gemm->an) || ttgt_saving_s(an, *one) <= kOneCopySavingS ||
-            (one->ws_bytes > COMET_NOALLOC_SCRATCH_BYTES && !(ttgt && one->ws_bytes <= tt->ws_bytes)))
+        if (ttgt_saving_s(an, c, true) <= kOneCopySavingS ||
+            build_plan(one, spec, extents, sA, sB, sC, dtype, compute, COMET_PATH_TTGT, false, &c) != COMET_OK ||
+            !one->gemm || !packed_reads(one->gemm->an))
           continue;
+        if (one->ws_bytes > COMET_NOALLOC_SCRATCH_BYTES) {
+          try_ttgt();
+          if (!ttgt || one->ws_bytes > tt->ws_bytes) continue;
+        }
         out = std::move(one);
         return COMET_OK;
       }
+    try_ttgt();
     if (ttgt) {
       out = std::move(tt);
       return COMET_OK;

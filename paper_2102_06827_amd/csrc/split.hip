@@ -147,7 +147,7 @@ __device__ __forceinline__ void load_tile(Tin *x, const Tin *__restrict__ base, 
 }
 
 // Gather a PR x PK tile into LDS (zeros outside the operand), in the storage
-// type: a CU then holds eight FP32 blocks instead of four, and the 1104 of a
+// type: a CU then holds five FP32 blocks instead of four, and the 1058 of a
 // 1452^3 product run in one round (the pack pass 18.8 us in FP64 tiles, 17.1 so).
 template <typename Tin, int LAYOUT, int V>
 __device__ __forceinline__ void gather_tile(Tin (*t)[PK + 1], const Tin *__restrict__ base, const int64_t *ro,
