@@ -53,15 +53,15 @@ EXT = dict(a=V, b=V, c=V, i=O, j=O, k=O)
 FLOPS = 2.0 * V ** 3 * O ** 3            # 2 * M * N * K, M = N = K = 3072
 PEAK_TFLOPS = {"f64": 78.6, "f32": 157.3, "bf16": 2516.6, "f16": 2516.6, "i8": 5033.2}
 HBM_PEAK_GBS = 8000.0
-# The headline contraction runs as one launch group of the gather kernel:
-# the whole output tiles and the summation pieces of the tiles left after
-# the last full round in one launch (gett_whole_piece_kernel; gett_kernel
-# and gett_sk_kernel when stream-K is planned instead), then the sum of
-# those pieces (gett_piece_fixup_kernel or gett_fixup_kernel).  HBM bytes of one group from FETCH_SIZE / WRITE_SIZE
+# The headline contraction runs as one launch group of the packed gather
+# kernel: the whole output tiles and the shares of the tiles left after the
+# last full round in one launch, then the sum of those shares' partial tiles
+# (packed_fixup_kernel; the vector-load tiles' kernels when those are planned
+# instead).  HBM bytes of one group from FETCH_SIZE / WRITE_SIZE
 # counters scaled by a plain 1 GiB copy (profiles/gett_f64_ccsd_v96_o32_hbm_counters.md);
 # valid only for the schedule and kernel version recorded, null otherwise.
-HEADLINE_TRAFFIC = {"schedule": {"tile": 3, "sk_tiles": 64, "sk_blocks": 512, "even": 1}, "kernel_version": "k11",
-                    "bytes": 971436304}
+HEADLINE_TRAFFIC = {"schedule": {"path": "gett", "packed": 1, "packed_whole": 512, "packed_shares": 256},
+                    "kernel_version": "k12", "bytes": 1112691917}
 KERNEL_VERSION = "k12"
 
 
