@@ -1386,7 +1386,8 @@ int split_shape(const Analysis &an, const SplitPlan &sp, bool large) {
     if (rest > 0) stage += std::max(X.alone[x], rest * X.full[x]);
     stage = std::max(stage, X.alone[x]);
     const double us = stages * stage + wgs * X.bm * X.bn * kSplitStoreUs[an.dtype == COMET_F64 ? 0 : 1];
-    const double bytes = 2.0 * sp.S * double(round_up(an.k, PK)) *
+    // the slices, and per row its exponent and about one partial of the pass
+    const double bytes = (2.0 * sp.S * double(round_up(an.k, PK)) + 8.0) *
                          (double(split_rows(an.m, X.bm)) + double(split_rows(an.n, X.bn)));
     const bool fits = bytes + (1 << 20) <= double(kSplitScratch);
     if (fits == best_fits ? us < best_us : fits) {
