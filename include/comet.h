@@ -132,7 +132,9 @@ typedef enum {
  *         operands only the gather path's element loads can read (their
  *         unit strides lie on different summation labels) where an estimate
  *         of the permutes' traffic and launches against the GEMM time they
- *         save says TTGT is faster (from about 768^3 on MI355X).
+ *         save says so: with one operand copied and the other and C used in
+ *         place where that lets both be read in runs, else with all three
+ *         permuted (from about 700^3 on MI355X).
  *   GETT  operands are gathered through per-label offset tables straight into
  *         on-chip tiles; no transposed copies are made.  A native product
  *         with one output row (the vector operand has no free label) streams
@@ -199,7 +201,7 @@ comet_status_t comet_contract(const char *spec, const int64_t *extents,
  * Pointer arguments of execute must satisfy the alignment the plan was
  * made for; misaligned pointers take the scalar gather, never an error.
  * The workspace holds TTGT's permuted operands, the split modes' slices, or
- * the partial sums of a stream-K or balanced schedule (output tiles whose
+ * the partial sums of a split schedule (output tiles whose
  * summation is split over several workgroups and summed afterwards in a
  * fixed order, so results do not depend on timing; the balanced schedule
  * cuts the tiles left after the last full round of whole tiles into one

@@ -129,7 +129,7 @@ int batch_blocks_per_cu(int dtype, int mode);
 // and the summation tables by kPackedKPad entries, with their last entry.
 // Tiles 0 .. whole - 1 (in the XCD-aware order) are computed by a workgroup
 // each; `shares` workgroups split the steps of the others, whose partial
-// tiles take 2 * shares * bm * bn elements of ws.
+// tiles take (shares + min(shares, others)) * bm * bn elements of ws.
 constexpr int kPackedTiles = 5;
 constexpr int kPackedRowPad = 128;
 constexpr int kPackedKPad = 160;
