@@ -510,12 +510,12 @@ __device__ __forceinline__ void stage_landed() {
 // stores share one in-order completion counter on CDNA.  With beta != 0 the C
 // values of the next group of four elements are requested before the current
 // group is stored.
-template <typename Tout, int BM, int BN, int FM, int FN, int NTH, typename ValF>
+template <bool STREAM, typename Tout, int BM, int BN, int FM, int FN, int NTH, typename ValF>
 __device__ __forceinline__ void split_store(Tout *__restrict__ C, const int64_t *__restrict__ offCm,
                                             const int64_t *__restrict__ offCn, const int *__restrict__ eA,
                                             const int *__restrict__ eB, int64_t M, int64_t N, double alpha,
-                                            double beta, int64_t m0, int64_t n0, int wm0, int wn0, int stream,
-                                            void *smem, ValF val) {
+                                            double beta, int64_t m0, int64_t n0, int wm0, int wn0, void *smem,
+                                            ValF val) {
   typedef typename std::conditional<sizeof(Tout) == 8, double, float>::type Te;
   lds_t<int64_t> *const toff = to_lds(static_cast<int64_t *>(smem));
   lds_t<int> *const texp = to_lds(reinterpret_cast<int *>(static_cast<int64_t *>(smem) + BM + BN));
@@ -542,59 +542,53 @@ __device__ __forceinline__ void split_store(Tout *__restrict__ C, const int64_t 
     const double prod = (em == kExpNone || en == kExpNone) ? 0.0 : ldexp(val(i, j, r), em + en);
     return Te(alpha * prod);
   };
-  auto pass = [&](auto streamed) {
-    auto put = [&](Tout v, int64_t at) {
-      if constexpr (decltype(streamed)::value)
-        __builtin_nontemporal_store(v, &gC[at]);
-      else
-        gC[at] = v;
-    };
-    if (beta == 0.0) {
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const int j = g / FM, i = g % FM;
-        int64_t a[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) a[r] = toff[ml(i, r)] + toff[BM + nl(j)];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (inside(i, r, j)) put(Tout(value(i, j, r)), a[r]);
-      }
-      return;
-    }
-    Tout cv[2][4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) cv[0][r] = gC[toff[ml(0, r)] + toff[BM + nl(0)]];
+  auto put = [&](Tout v, int64_t at) {
+    if constexpr (STREAM)
+      __builtin_nontemporal_store(v, &gC[at]);
+    else
+      gC[at] = v;
+  };
+  if (beta == 0.0) {
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const int j = g / FM, i = g % FM;
-      __builtin_amdgcn_sched_barrier(0);
-      if (g + 1 < G) {
-        const int j1 = (g + 1) / FM, i1 = (g + 1) % FM;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) cv[(g + 1) & 1][r] = gC[toff[ml(i1, r)] + toff[BM + nl(j1)]];
-      }
       int64_t a[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) a[r] = toff[ml(i, r)] + toff[BM + nl(j)];
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (inside(i, r, j)) put(Tout(value(i, j, r) + Te(beta) * Te(cv[g & 1][r])), a[r]);
+        if (inside(i, r, j)) put(Tout(value(i, j, r)), a[r]);
     }
-  };
-  if (stream)
-    pass(std::true_type{});
-  else
-    pass(std::false_type{});
+    return;
+  }
+  Tout cv[2][4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) cv[0][r] = gC[toff[ml(0, r)] + toff[BM + nl(0)]];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int j = g / FM, i = g % FM;
+    __builtin_amdgcn_sched_barrier(0);
+    if (g + 1 < G) {
+      const int j1 = (g + 1) / FM, i1 = (g + 1) % FM;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) cv[(g + 1) & 1][r] = gC[toff[ml(i1, r)] + toff[BM + nl(j1)]];
+    }
+    int64_t a[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a[r] = toff[ml(i, r)] + toff[BM + nl(j)];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (inside(i, r, j)) put(Tout(value(i, j, r) + Te(beta) * Te(cv[g & 1][r])), a[r]);
+  }
 }
 
-template <typename ST, typename Tout, int MODE, int S>
+template <typename ST, typename Tout, int MODE, int S, bool STREAM>
 __global__ __launch_bounds__(GNT) void split_gemm_kernel(const ST *__restrict__ As, const ST *__restrict__ Bs,
                                                           const int *__restrict__ eA, const int *__restrict__ eB,
                                                           Tout *__restrict__ C, const int64_t *__restrict__ offCm,
                                                           const int64_t *__restrict__ offCn, int64_t M, int64_t N,
                                                           int64_t Mp, int64_t Np, int64_t Kp, double alpha,
-                                                          double beta, int tilesM, int tilesN, int stream) {
+                                                          double beta, int tilesM, int tilesN) {
   typedef Pairs<MODE, S> PP;
   typedef typename Vec8<ST>::type v8;
   constexpr int WM = GBM / GWM, WN = GBN / GWN;      // 32 x 32
@@ -754,7 +748,7 @@ __global__ __launch_bounds__(GNT) void split_gemm_kernel(const ST *__restrict__ 
 
   // epilogue: C = alpha * 2^(eA + eB) * acc + beta * C
   static_assert((GBM + GBN) * 12 <= STAGE * int(sizeof(ST)), "epilogue tables fit in LDS");
-  split_store<Tout, GBM, GBN, FM, FN, GNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, stream,
+  split_store<STREAM, Tout, GBM, GBN, FM, FN, GNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0,
                                           NBUF == 2 ? static_cast<void *>(smem0_) : static_cast<void *>(smem),
                                           [&](int i, int j, int r) { return acc64[i][j][r]; });
 }
@@ -792,7 +786,7 @@ constexpr SplitShape kSplitShapes[] = {
 };
 constexpr double kSplitStoreUs[2] = {0.34e-3, 0.2e-3};   // per output of a CU's workgroups: FP64, FP32
 
-template <typename ST, typename Tout, int MODE, int S, int SHAPE>
+template <typename ST, typename Tout, int MODE, int S, int SHAPE, bool STREAM>
 __global__ __launch_bounds__(64 * kSplitShapes[SHAPE].wgm * kSplitShapes[SHAPE].wgn,
                              kSplitShapes[SHAPE].wgm * kSplitShapes[SHAPE].wgn * kSplitShapes[SHAPE].wgs[0] / 4) void
 split_gemm_big_kernel(const ST *__restrict__ As, const ST *__restrict__ Bs,
@@ -800,7 +794,7 @@ split_gemm_big_kernel(const ST *__restrict__ As, const ST *__restrict__ Bs,
                                                               Tout *__restrict__ C, const int64_t *__restrict__ offCm,
                                                               const int64_t *__restrict__ offCn, int64_t M, int64_t N,
                                                               int64_t Mp, int64_t Np, int64_t Kp, double alpha,
-                                                              double beta, int tilesM, int tilesN, int stream) {
+                                                              double beta, int tilesM, int tilesN) {
   constexpr int XBM = kSplitShapes[SHAPE].bm, XBN = kSplitShapes[SHAPE].bn;
   constexpr int XWM = kSplitShapes[SHAPE].wgm, XWN = kSplitShapes[SHAPE].wgn, XNT = 64 * XWM * XWN;
   typedef Pairs<MODE, S> PP;
@@ -898,7 +892,7 @@ split_gemm_big_kernel(const ST *__restrict__ As, const ST *__restrict__ Bs,
 
   // epilogue: C = alpha * 2^(eA + eB) * sum_a scale(a) * acc[a] + beta * C
   static_assert((XBM + XBN) * 12 <= STAGE * int(sizeof(ST)), "epilogue tables fit in LDS");
-  split_store<Tout, XBM, XBN, FM, FN, XNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, stream, smem0_,
+  split_store<STREAM, Tout, XBM, XBN, FM, FN, XNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, smem0_,
                                           [&](int i, int j, int r) {
                                             double sum = 0.0;
 #pragma unroll
@@ -932,13 +926,13 @@ constexpr int WNT = 64 * WWM * WWN;
 // twice in LDS
 constexpr bool wide_tile_fits(int S) { return 2 * S * (WBM + WBN) * 64 <= 160 * 1024; }
 
-template <typename ST, typename Tout, int MODE, int S>
+template <typename ST, typename Tout, int MODE, int S, bool STREAM>
 __global__ __launch_bounds__(WNT) void split_gemm_wide_kernel(const ST *__restrict__ As, const ST *__restrict__ Bs,
                                                                const int *__restrict__ eA, const int *__restrict__ eB,
                                                                Tout *__restrict__ C, const int64_t *__restrict__ offCm,
                                                                const int64_t *__restrict__ offCn, int64_t M, int64_t N,
                                                                int64_t Mp, int64_t Np, int64_t Kp, double alpha,
-                                                               double beta, int tilesM, int tilesN, int stream) {
+                                                               double beta, int tilesM, int tilesN) {
   typedef Pairs<MODE, S> PP;
   static_assert(MODE == 0 && PP::NACC == 3 && PP::FOLD == 4, "the wide tile is for the aligned split");
   static_assert(wide_tile_fits(S), "two stages must fit in LDS");
@@ -1098,7 +1092,7 @@ __global__ __launch_bounds__(WNT) void split_gemm_wide_kernel(const ST *__restri
   // (the last stage's barrier passed: both buffers are free, the clamped
   // loads past the end landed)
   static_assert((WBM + WBN) * 12 <= STAGE * int(sizeof(ST)), "epilogue tables fit in LDS");
-  split_store<Tout, WBM, WBN, FM, FN, WNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, stream, smem0_,
+  split_store<STREAM, Tout, WBM, WBN, FM, FN, WNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, smem0_,
                                           [&](int i, int j, int r) { return acc64[i][j][r]; });
 }
 
@@ -1252,7 +1246,7 @@ __global__ __launch_bounds__(GNT) void split_gemm_i8_kernel(const signed char *_
   // (after an odd last stage, buffer 0 is still being read: wait for every
   // wave before its first bytes take the epilogue tables)
   if constexpr (NBUF == 2) __syncthreads();
-  split_store<Tout, GBM, GBN, FM, FN, GNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0, 1,
+  split_store<true, Tout, GBM, GBN, FM, FN, GNT>(C, offCm, offCn, eA, eB, M, N, alpha, beta, m0, n0, wm0, wn0,
                                           NBUF == 2 ? static_cast<void *>(smem0_) : static_cast<void *>(smem),
                                           [&](int i, int j, int r) {
                                             double sum = 0.0;
@@ -1296,7 +1290,10 @@ hipError_t run_split(const Analysis &an, const SplitPlan &sp, const GettTables &
   // C past the caches (nontemporal stores) where it comes in whole 64-byte
   // segments; a segment stored in parts that way costs a memory round trip
   // for each (a 192 x 192 tile's FP64 epilogue: 43 us, 14 through the caches)
-  const int stream = sp.segments && reinterpret_cast<uintptr_t>(C) % 64 == 0;
+  // (a kernel for each: with both epilogues in one kernel the K = 32, 8192 x
+  // 16384 products take 424 us in aligned BF16, 396 so, and in FP32 BF16x3, 128
+  // x 128 tiles, 276 us, 243 so)
+  const bool stream = sp.segments && reinterpret_cast<uintptr_t>(C) % 64 == 0;
   if constexpr (MODE == 3) {
     // exact int32 diagonal sums over at most IKC indices per launch; later
     // launches add into C
@@ -1306,39 +1303,48 @@ hipError_t run_split(const Analysis &an, const SplitPlan &sp, const GettTables &
                          static_cast<Tin *>(C), t.offCm, t.offCn, an.m, an.n, sp.Mp, sp.Np, sp.Kp, k0, len, alpha,
                          k0 == 0 ? beta : 1.0, tilesM, tilesN);
     }
-  } else if (sp.tile == 2) {
-    if constexpr (MODE == 0 && wide_tile_fits(S)) {
-      hipLaunchKernelGGL((split_gemm_wide_kernel<ST, Tin, MODE, S>), dim3(int(sp.Mp / WBM) * int(sp.Np / WBN)),
-                         dim3(WNT), 0, s, As, Bs, eA, eB, static_cast<Tin *>(C), t.offCm, t.offCn, an.m, an.n, sp.Mp,
-                         sp.Np, sp.Kp, alpha, beta, int(sp.Mp / WBM), int(sp.Np / WBN), stream);
-    } else {
-      return hipErrorInvalidValue;
-    }
-  } else if (sp.shape > 0) {
-    if constexpr (Pairs<MODE, S>::FOLD == 0) {
-      auto launch = [&](auto shape) {
-        constexpr SplitShape X = kSplitShapes[shape.value];
-        const int tm = int((an.m + X.bm - 1) / X.bm), tn = int((an.n + X.bn - 1) / X.bn);
-        hipLaunchKernelGGL((split_gemm_big_kernel<ST, Tin, MODE, S, shape.value>), dim3(tm * tn),
-                           dim3(64 * X.wgm * X.wgn), 0, s, As, Bs, eA, eB, static_cast<Tin *>(C), t.offCm, t.offCn,
-                           an.m, an.n, sp.Mp, sp.Np, sp.Kp, alpha, beta, tm, tn, stream);
-      };
-      if (sp.shape == 1)
-        launch(std::integral_constant<int, 1>{});
-      else if (sp.shape == 2)
-        launch(std::integral_constant<int, 2>{});
-      else if (sp.shape == 3)
-        launch(std::integral_constant<int, 3>{});
-      else
-        launch(std::integral_constant<int, 4>{});
-    } else {
-      return hipErrorInvalidValue;
-    }
-  } else
-    hipLaunchKernelGGL((split_gemm_kernel<ST, Tin, MODE, S>), dim3(tilesM * tilesN), dim3(GNT), 0, s, As, Bs, eA,
-                       eB, static_cast<Tin *>(C), t.offCm, t.offCn, an.m, an.n, sp.Mp, sp.Np, sp.Kp, alpha, beta,
-                       tilesM, tilesN, stream);
-  return hipGetLastError();
+    return hipGetLastError();
+  } else {
+    auto product = [&](auto streamed) -> hipError_t {
+      constexpr bool STREAM = decltype(streamed)::value;
+      if (sp.tile == 2) {
+        if constexpr (MODE == 0 && wide_tile_fits(S)) {
+          hipLaunchKernelGGL((split_gemm_wide_kernel<ST, Tin, MODE, S, STREAM>),
+                             dim3(int(sp.Mp / WBM) * int(sp.Np / WBN)), dim3(WNT), 0, s, As, Bs, eA, eB,
+                             static_cast<Tin *>(C), t.offCm, t.offCn, an.m, an.n, sp.Mp, sp.Np, sp.Kp, alpha, beta,
+                             int(sp.Mp / WBM), int(sp.Np / WBN));
+        } else {
+          return hipErrorInvalidValue;
+        }
+      } else if (sp.shape > 0) {
+        if constexpr (Pairs<MODE, S>::FOLD == 0) {
+          auto launch = [&](auto shape) {
+            constexpr SplitShape X = kSplitShapes[shape.value];
+            const int tm = int((an.m + X.bm - 1) / X.bm), tn = int((an.n + X.bn - 1) / X.bn);
+            hipLaunchKernelGGL((split_gemm_big_kernel<ST, Tin, MODE, S, shape.value, STREAM>), dim3(tm * tn),
+                               dim3(64 * X.wgm * X.wgn), 0, s, As, Bs, eA, eB, static_cast<Tin *>(C), t.offCm,
+                               t.offCn, an.m, an.n, sp.Mp, sp.Np, sp.Kp, alpha, beta, tm, tn);
+          };
+          if (sp.shape == 1)
+            launch(std::integral_constant<int, 1>{});
+          else if (sp.shape == 2)
+            launch(std::integral_constant<int, 2>{});
+          else if (sp.shape == 3)
+            launch(std::integral_constant<int, 3>{});
+          else
+            launch(std::integral_constant<int, 4>{});
+        } else {
+          return hipErrorInvalidValue;
+        }
+      } else {
+        hipLaunchKernelGGL((split_gemm_kernel<ST, Tin, MODE, S, STREAM>), dim3(tilesM * tilesN), dim3(GNT), 0, s, As,
+                           Bs, eA, eB, static_cast<Tin *>(C), t.offCm, t.offCn, an.m, an.n, sp.Mp, sp.Np, sp.Kp,
+                           alpha, beta, tilesM, tilesN);
+      }
+      return hipGetLastError();
+    };
+    return stream ? product(std::true_type{}) : product(std::false_type{});
+  }
 }
 
 template <typename Tin>
