@@ -776,13 +776,16 @@ struct SplitShape {
   // stage and workgroup of a full CU
   int wgs[2];
   double alone[2], full[2];
+  // us more of a CU's workgroup beyond its first round: the prologue and
+  // epilogue that a workgroup alone on its CU has nothing to hide under
+  double more[2];
 };
 constexpr SplitShape kSplitShapes[] = {
-    {128, 64, 4, 2, {2, 3}, {0.72, 0.49}, {0.610, 0.360}},   // 0: split_gemm_kernel
-    {192, 192, 2, 4, {1, 1}, {1.95, 1.15}, {2.22, 1.27}},    // 1
-    {128, 128, 2, 4, {1, 2}, {0.95, 0.60}, {1.07, 0.600}},   // 2
-    {96, 96, 2, 2, {2, 3}, {0.70, 0.56}, {0.655, 0.375}},    // 3
-    {64, 64, 2, 2, {3, 5}, {0.50, 0.40}, {0.335, 0.200}},    // 4
+    {128, 64, 4, 2, {2, 3}, {0.72, 0.49}, {0.610, 0.360}, {0.5, 0.0}},   // 0: split_gemm_kernel
+    {192, 192, 2, 4, {1, 1}, {1.95, 1.15}, {2.22, 1.27}, {2.0, 0.0}},     // 1
+    {128, 128, 2, 4, {1, 2}, {0.95, 0.60}, {1.07, 0.600}, {2.5, 0.0}},    // 2
+    {96, 96, 2, 2, {2, 3}, {0.70, 0.56}, {0.655, 0.375}, {0.4, 0.0}},     // 3
+    {64, 64, 2, 2, {3, 5}, {0.50, 0.40}, {0.335, 0.200}, {0.2, 0.0}},     // 4
 };
 constexpr double kSplitStoreUs[2] = {0.34e-3, 0.2e-3};   // per output of a CU's workgroups: FP64, FP32
 
@@ -1381,7 +1384,13 @@ int64_t split_rows(int64_t rows, int64_t tile) { return round_up(round_up(rows, 
 // the busiest CU's workgroups in rounds of as many as it holds, each stage
 // of a round at the measured rate (a round with few workgroups takes one
 // workgroup's own time), and their outputs' stores.  Its times lie within 8%
-// of the measured kernel over 64 to 1536 tiles of every shape.  `large`:
+// of the measured kernel over 64 to 1536 tiles of every shape; beyond, on
+// short summations, what a further workgroup costs besides its stages decides
+// (BF16x3, K = 32, 8192 x 16384: 128 x 128 tiles, a workgroup per CU, 218 us in
+// FP32 and 232 in FP64, 128 x 64 176 and 196, 192 x 192 186 and 207).  With
+// `more` the BF16x3 pick is at most 1% slower than 192 x 192 tiles over 60
+// outputs of 9 million elements and more, K from 64 to 1024 (19% without);
+// FP16x2, whose CUs hold two 128 x 128 workgroups, needs none.  `large`:
 // whether 192 x 192 tiles may be taken.  A shape whose slices need more
 // than kSplitScratch of workspace, which an execution without allocation may
 // not use, is taken only if every shape needs as much.
@@ -1389,6 +1398,10 @@ constexpr int64_t kSplitScratch = int64_t(128) << 20;
 int split_shape(const Analysis &an, const SplitPlan &sp, bool large) {
   const int x = sp.mode - 1;
   const double stages = double(round_up(an.k, PK) / GBK);
+  int device = 0, cus = 256;
+  if (hipGetDevice(&device) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1)
+    cus = 256;
   int best = 0;
   double best_us = 1e300;
   bool best_fits = false;
@@ -1396,11 +1409,12 @@ int split_shape(const Analysis &an, const SplitPlan &sp, bool large) {
     const SplitShape &X = kSplitShapes[i];
     if (i == 1 && !large) continue;
     const double tiles = double(round_up(an.m, X.bm) / X.bm) * double(round_up(an.n, X.bn) / X.bn);
-    const double wgs = std::ceil(tiles / 256), rounds = std::floor(wgs / X.wgs[x]), rest = wgs - rounds * X.wgs[x];
+    const double wgs = std::ceil(tiles / cus), rounds = std::floor(wgs / X.wgs[x]), rest = wgs - rounds * X.wgs[x];
     double stage = rounds * X.wgs[x] * X.full[x];
     if (rest > 0) stage += std::max(X.alone[x], rest * X.full[x]);
     stage = std::max(stage, X.alone[x]);
-    const double us = stages * stage + wgs * X.bm * X.bn * kSplitStoreUs[an.dtype == COMET_F64 ? 0 : 1];
+    const double us = stages * stage + wgs * X.bm * X.bn * kSplitStoreUs[an.dtype == COMET_F64 ? 0 : 1] +
+                      std::max(0.0, wgs - X.wgs[x]) * X.more[x];
     // the slices, and per row its exponent and about one partial of the pass
     const double bytes = (2.0 * sp.S * double(round_up(an.k, PK)) + 8.0) *
                          (double(split_rows(an.m, X.bm)) + double(split_rows(an.n, X.bn)));
