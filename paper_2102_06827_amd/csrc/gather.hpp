@@ -493,7 +493,9 @@ __device__ __forceinline__ void gett_accumulate(WaveTile<Tc, BM, BN, WGM, WGN> &
 // the compiler can wait for loads issued before them without waiting for the
 // stores themselves (a skipped store makes that count unknown, and every
 // later wait a full one).
-// STREAM: nontemporal stores (see above); else plain ones.
+// STREAM: nontemporal stores (see above); else plain ones.  tid: the thread's
+// index (a kernel that loops over tiles may hide it from the compiler, see
+// packed_kernel).
 template <typename T, bool STREAM>
 __device__ __forceinline__ void store_c(T v, glb_t<T> *p) {
   if constexpr (STREAM)
@@ -505,11 +507,11 @@ template <typename Tin, typename Tc, int BM, int BN, int WGM, int WGN, bool SINK
 __device__ __forceinline__ void gett_store_staged(const WaveTile<Tc, BM, BN, WGM, WGN> &w, Tin *__restrict__ C,
                                                   const lds_t<int64_t> *cm, const lds_t<int64_t> *cn, int64_t M,
                                                   int64_t N, double alpha, double beta, int64_t m0, int64_t n0,
-                                                  Tin *sink = nullptr) {
+                                                  Tin *sink = nullptr, int tid = int(threadIdx.x)) {
   typedef WaveTile<Tc, BM, BN, WGM, WGN> WT;
   typedef typename std::conditional<(sizeof(Tin) == 8 || sizeof(Tc) == 8), double, float>::type Te;
   constexpr int G = WT::FN * WT::FM;   // groups of four elements: (j, i)
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave / WGN) * WT::WM, wn0 = (wave % WGN) * WT::WN;
   const Te al = Te(alpha), be = Te(beta);
   glb_t<Tin> *const gC = to_glb(C);

@@ -138,13 +138,21 @@ packed_kernel(PackedLaunch g) {
     int tm, tn;
     group_coords(is_whole ? xcd_remap(b, g.whole) : g.whole + tt, g.tilesM, g.tilesN, &tm, &tn);
     const int m0 = __builtin_amdgcn_readfirstlane(tm * P::BM), n0 = __builtin_amdgcn_readfirstlane(tn * P::BN);
+    // (What depends on the thread alone is the same for every piece: the
+    // compiler would work the epilogue's addresses out ahead of the loop, hold
+    // them over the products and, in the FP64 128 x 128 kernels, spill 25 to 32
+    // of them.  A thread index it cannot see through keeps them where they are
+    // used: FP64 3072^3 848 -> 828 us, no scratch.)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
     WT w;
     typename P::COffsets co;
-    co.load(threadIdx.x, g.c, m0, n0, g.M, g.N);
-    P::accumulate(w, ra, rb, g.am + m0, g.ak, g.bk, g.bn + n0, s0, s1, to_lds(smem), co, ctab);
+    co.load(tid, g.c, m0, n0, g.M, g.N);
+    P::accumulate(w, ra, rb, g.am + m0, g.ak, g.bk, g.bn + n0, s0, s1, to_lds(smem), co, ctab, tid);
+    asm volatile("" : "+v"(tid));
     if (s1 - s0 == nk) {
-      gett_store_staged<T, T, P::BM, P::BN, P::WGM, P::WGN, false, STREAM>(w, C, ctab, ctab + P::BM, g.M, g.N,
-                                                            g.alpha, g.beta, m0, n0);
+      gett_store_staged<T, T, P::BM, P::BN, P::WGM, P::WGN, false, STREAM>(
+          w, C, ctab, ctab + P::BM, g.M, g.N, g.alpha, g.beta, m0, n0, nullptr, tid);
       __syncthreads();   // the C offsets are read before the next piece's are stored
     } else {
       constexpr int64_t kSlot = int64_t(WT::FM) * WT::FN * WT::NT;   // 4-vectors per slot

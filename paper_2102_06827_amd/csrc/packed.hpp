@@ -164,8 +164,8 @@ struct PackedCore {
   static __device__ __forceinline__ void accumulate(WT &w, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb,
                                                     const uint32_t *am, const uint32_t *ak, const uint32_t *bk,
                                                     const uint32_t *bn, int s0, int s1, lds_t<T> *smem,
-                                                    const COffsets &co, lds_t<int64_t> *ctab) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                                    const COffsets &co, lds_t<int64_t> *ctab, int tid = int(threadIdx.x)) {
+    const int lane = tid & 63, wave = tid >> 6;
     lds_t<T> *const sB = smem + 2 * LoadA::ELEMS;
     const int fa = ((wave / WGN) * WT::WM + (lane & 15)) * LDK + (lane >> 4) * VL;
     const int fb = ((wave % WGN) * WT::WN + (lane & 15)) * LDK + (lane >> 4) * VL;
