@@ -84,9 +84,26 @@ constexpr PackedTile packed_tile(int tile) {
   return sizeof(T) == 8 ? kPacked64[tile] : kPacked32[tile];
 }
 
+// FP32 accumulators of a tile (see PackedCore): eight sets on the tiles of
+// small and mid-size products, a fold every 128 summation indices on 64 x 64
+// and 128 x 64 and every 512 on 128 x 128.  A whole tile would carry all of K
+// in one accumulator, and its error grows by the root of that chain; a
+// schedule that fills the chip with whole tiles is not to cost the accuracy
+// that splitting the summation over workgroups had.  Relative error (uniform
+// operands) and time, one accumulator / so: 256^3 2.9e-7 / 1.1e-7, 7.1 / 7.4
+// us; 512^3 4.1e-7 / 1.5e-7, 11.1 / 11.5; 960^3 5.6e-7 / 2.0e-7; 1200^3 6.2e-7
+// / 2.2e-7, 43.9 / 44.3; 1725^3 7.4e-7 / 2.1e-7, 108 / 109; 3072^3 9.5e-7 /
+// 4.0e-7, 440 / 441.  (A fold every step or two on the small tiles: 256^3 7.3
+// to 7.6 us, 512^3 11.6 to 12.2, 1200^3 45.3 to 46.7.)
+constexpr int kSets32[] = {1, 1, 1, 8, 8}, kFold32[] = {16, 4, 4, 0, 0};
+template <typename T>
+constexpr int packed_sets(int tile) { return sizeof(T) == 8 ? 1 : kSets32[tile]; }
+template <typename T>
+constexpr int packed_fold(int tile) { return sizeof(T) == 8 ? 0 : kFold32[tile]; }
 template <typename T, int TILE, int LA, int LB>
 using PackedKernel = PackedCore<T, packed_tile<T>(TILE).bm, packed_tile<T>(TILE).bn, packed_tile<T>(TILE).bk,
-                                packed_tile<T>(TILE).wgm, packed_tile<T>(TILE).wgn, LA, LB>;
+                                packed_tile<T>(TILE).wgm, packed_tile<T>(TILE).wgn, LA, LB, packed_sets<T>(TILE),
+                                packed_fold<T>(TILE)>;
 
 // The workspace slot of share s's piece of shared tile t.  Along the steps
 // each piece has a larger s or a larger t than the one before, so s + t

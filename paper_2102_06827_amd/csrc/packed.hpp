@@ -102,8 +102,11 @@ struct PackedLoader {
 };
 
 // A workgroup of WGM x WGN waves on a BM x BN output tile in summation steps
-// of BK.
-template <typename T, int BM_, int BN_, int BK_, int WGM_, int WGN_, int LA, int LB>
+// of BK.  How long a chain of rounded additions gets: with SETS = 2 * VL each
+// of a step's products into an output fragment has an accumulator of its own
+// (one in 2 * VL summation indices), the sets added at the end; with FOLD > 0
+// the accumulators are added into a second set and cleared every FOLD steps.
+template <typename T, int BM_, int BN_, int BK_, int WGM_, int WGN_, int LA, int LB, int SETS = 1, int FOLD = 0>
 struct PackedCore {
   static constexpr int BM = BM_, BN = BN_, BK = BK_, WGM = WGM_, WGN = WGN_;
   static constexpr int NT = 64 * WGM * WGN;
@@ -128,8 +131,12 @@ struct PackedCore {
     }
   };
 
-  // the products of chunk c of a step
-  static __device__ __forceinline__ void mma(WT &w, const lds_t<T> *a, const lds_t<T> *b, int c) {
+  static_assert(SETS == 1 || (SETS == 2 * VL && FOLD == 0), "one set, or one for each product of a step");
+  typedef typename WT::acc_t Acc[WT::FM][WT::FN];
+
+  // the products of chunk c of a step; with SETS > 1 product
+  // (c, x) into set c * VL + x, set 0 being w's and the others `more`
+  static __device__ __forceinline__ void mma(WT &w, Acc *more, const lds_t<T> *a, const lds_t<T> *b, int c) {
     typedef typename LoadA::vec_t vec_t;
     vec_t af[WT::FM], bf[WT::FN];
 #pragma unroll
@@ -141,7 +148,10 @@ struct PackedCore {
 #pragma unroll
       for (int i = 0; i < WT::FM; ++i)
 #pragma unroll
-        for (int j = 0; j < WT::FN; ++j) w.acc[i][j] = mfma16(af[i][x], bf[j][x], w.acc[i][j]);
+        for (int j = 0; j < WT::FN; ++j) {
+          typename WT::acc_t &acc = SETS == 1 || c * VL + x == 0 ? w.acc[i][j] : more[c * VL + x - 1][i][j];
+          acc = mfma16(af[i][x], bf[j][x], acc);
+        }
   }
   static constexpr int READS = WT::FM + WT::FN, MMAS = WT::FM * WT::FN * VL;
 
@@ -196,15 +206,23 @@ struct PackedCore {
     la.fetch_k(ak, (s0 + 2) * BK);
     lb.fetch_k(bk, (s0 + 2) * BK);
     __syncthreads();
+    constexpr int MORE = SETS > 1 ? SETS - 1 : FOLD > 0 ? 1 : 0;
+    Acc more[MORE > 0 ? MORE : 1];
+#pragma unroll
+    for (int q = 0; q < MORE; ++q)
+#pragma unroll
+      for (int i = 0; i < WT::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < WT::FN; ++j) more[q][i][j] = typename WT::acc_t{0, 0, 0, 0};
     int buf = 0;
-    for (int s = s0; s < s1; ++s) {
+    auto step = [&](int s) {
       const lds_t<T> *a = smem + buf * LoadA::ELEMS + fa, *b = sB + buf * LoadB::ELEMS + fb;
-      mma(w, a, b, 0);
+      mma(w, more, a, b, 0);
       la.store(smem + (buf ^ 1) * LoadA::ELEMS);
       lb.store(sB + (buf ^ 1) * LoadB::ELEMS);
       schedule<0x200, LoadA::WRITES + LoadB::WRITES>();
       __builtin_amdgcn_sched_barrier(0);
-      mma(w, a, b, 1);
+      mma(w, more, a, b, 1);
       la.load(ra);
       lb.load(rb);
       schedule<0x20, LoadA::PER + LoadB::PER>();
@@ -213,6 +231,36 @@ struct PackedCore {
       lb.fetch_k(bk, (s + 3) * BK);
       __syncthreads();
       buf ^= 1;
+    };
+    if constexpr (FOLD == 0) {
+      for (int s = s0; s < s1; ++s) step(s);
+    } else {
+      for (int s = s0; s < s1;) {
+        const int e = s1 - s < FOLD ? s1 : s + FOLD;
+        for (; s < e; ++s) step(s);
+#pragma unroll
+        for (int i = 0; i < WT::FM; ++i)
+#pragma unroll
+          for (int j = 0; j < WT::FN; ++j) {
+            more[0][i][j] += w.acc[i][j];
+            w.acc[i][j] = typename WT::acc_t{0, 0, 0, 0};
+          }
+      }
+    }
+    // (pairs of sets, then pairs of those)
+#pragma unroll
+    for (int d = 1; d < SETS; d *= 2)
+#pragma unroll
+      for (int q = 0; q < SETS; q += 2 * d)
+#pragma unroll
+        for (int i = 0; i < WT::FM; ++i)
+#pragma unroll
+          for (int j = 0; j < WT::FN; ++j) (q ? more[q - 1][i][j] : w.acc[i][j]) += more[q + d - 1][i][j];
+    if constexpr (FOLD > 0) {
+#pragma unroll
+      for (int i = 0; i < WT::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < WT::FN; ++j) w.acc[i][j] = more[0][i][j];
     }
   }
 };
