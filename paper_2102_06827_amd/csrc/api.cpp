@@ -993,7 +993,7 @@ comet_status_t build_plan(std::unique_ptr<comet_plan_s> &out, const char *spec, 
   // Only tile 1's element-load kernel can gather these operands (their unit
   // strides lie on different summation labels, or runs are ragged): when the
   // estimate says the permutes of TTGT cost less than that kernel, take TTGT.
-  // This is the untuned default only: with the autotuner on it times both
+  // This is the untuned default only: the autotuner times it with the others
   // (or reads its cache), and a forced gather schedule keeps the gather path.
   const bool tuning = tune && tune_cache().mode() != 0;
   const bool gather_forced = std::getenv("COMET_GETT_TILE") || std::getenv("COMET_GETT_SK") ||
@@ -1544,7 +1544,13 @@ comet_status_t autotune_plan(std::unique_ptr<comet_plan_s> &p, const char *spec,
       if (an.packed > 0 && p->sk_bytes > skws_bytes) {
         if (skws) (void)hipFree(skws);
         skws = nullptr;
-        skws_bytes = hipMalloc(&skws, p->sk_bytes) == hipSuccess ? p->sk_bytes : 0;
+        skws_bytes = 0;
+        if (hipMalloc(&skws, p->sk_bytes) == hipSuccess) {
+          skws_bytes = p->sk_bytes;
+        } else {
+          skws = nullptr;
+          (void)hipGetLastError();   // not the next launch's error
+        }
       }
       if (an.packed > 0 && p->sk_bytes <= skws_bytes) {
         bool good;
@@ -1555,7 +1561,34 @@ comet_status_t autotune_plan(std::unique_ptr<comet_plan_s> &p, const char *spec,
           best.packed = 1;
         }
       }
+      auto time_lowering = [&](const comet_plan_s *cp, int untuned) {
+        if (cp->ws_bytes > wsb) {
+          if (ws) (void)hipFree(ws);
+          ws = nullptr;
+          wsb = 0;
+          if (hipMalloc(&ws, cp->ws_bytes) != hipSuccess) {
+            ws = nullptr;
+            (void)hipGetLastError();
+            return;
+          }
+          wsb = cp->ws_bytes;
+        }
+        bool good;
+        double us = time_us([&]() { return execute(cp, 1.0, bufA, bufB, 0.0, bufC, ws, wsb, s); }, s, &good);
+        if (good && us < best.us) {
+          const TTGTChoice &ch = cp->an.ttgt;
+          best = TuneEntry{cp->gemm ? cp->gemm->an.tile : 0, COMET_PATH_TTGT, us,
+                           ch.a_order + "|" + ch.b_order + "|" + ch.c_order};
+          best.packed = untuned;
+        }
+      };
       if (tt) {
+        // the lowering of a plan without tuning, where that is none of the
+        // flattenings below: one operand copied, C written in place
+        std::unique_ptr<comet_plan_s> untuned;
+        if (build_plan(untuned, spec, extents, sA, sB, sC, an.dtype, an.compute, COMET_PATH_AUTO, false) == COMET_OK &&
+            untuned->an.path == COMET_PATH_TTGT)
+          time_lowering(untuned.get(), 1);
         // every TTGT flattening, cheapest by the cost model first, up to
         // kTuneTTGT of them (the model ranks them poorly on MI355X, so it only
         // orders the search)
@@ -1563,26 +1596,9 @@ comet_status_t autotune_plan(std::unique_ptr<comet_plan_s> &p, const char *spec,
         if (cands.size() > size_t(kTuneTTGT)) cands.resize(kTuneTTGT);
         for (const TTGTChoice &ch : cands) {
           std::unique_ptr<comet_plan_s> cp;
-          if (build_plan(cp, spec, extents, sA, sB, sC, an.dtype, an.compute, COMET_PATH_TTGT, false, &ch) !=
+          if (build_plan(cp, spec, extents, sA, sB, sC, an.dtype, an.compute, COMET_PATH_TTGT, false, &ch) ==
               COMET_OK)
-            continue;
-          if (cp->ws_bytes > wsb) {
-            if (ws) (void)hipFree(ws);
-            ws = nullptr;
-            wsb = 0;
-            if (hipMalloc(&ws, cp->ws_bytes) != hipSuccess) {
-              ws = nullptr;
-              continue;
-            }
-            wsb = cp->ws_bytes;
-          }
-          bool good;
-          const comet_plan_s *pt = cp.get();
-          double us = time_us([&]() { return execute(pt, 1.0, bufA, bufB, 0.0, bufC, ws, wsb, s); }, s, &good);
-          if (good && us < best.us) {
-            best = TuneEntry{cp->gemm ? cp->gemm->an.tile : 0, COMET_PATH_TTGT, us,
-                             ch.a_order + "|" + ch.b_order + "|" + ch.c_order};
-          }
+            time_lowering(cp.get(), 0);
         }
       }
       (void)hipStreamSynchronize(s);
@@ -1597,7 +1613,15 @@ comet_status_t autotune_plan(std::unique_ptr<comet_plan_s> &p, const char *spec,
     if (!ok || best.us >= 1e30) return COMET_OK;   // tuning not possible: keep the heuristic
     tc.store(key, best);
   }
-  if (best.path == COMET_PATH_TTGT) {
+  if (best.path == COMET_PATH_TTGT && best.packed) {
+    // the untuned plan's own lowering (if this problem of the class has one)
+    std::unique_ptr<comet_plan_s> untuned;
+    if (build_plan(untuned, spec, extents, sA, sB, sC, an.dtype, an.compute, COMET_PATH_AUTO, false) == COMET_OK &&
+        untuned->an.path == COMET_PATH_TTGT) {
+      p = std::move(untuned);
+      return COMET_OK;
+    }
+  } else if (best.path == COMET_PATH_TTGT) {
     // the recorded flattening, if it is still one of this problem's
     const TTGTChoice *forced = nullptr;
     std::vector<TTGTChoice> cands = ttgt_candidates(an);

@@ -16,8 +16,9 @@ struct TuneEntry {
   int path = COMET_PATH_GETT;
   double us = 0.0;
   std::string ttgt;   // for path TTGT: "A order|B order|C order" of the fastest flattening
-  // nonzero: the packed gather kernel, by its own schedule (tile is then the
-  // gather tile it stands in for)
+  // nonzero: what an untuned plan does.  Path GETT: the packed gather kernel,
+  // by its own schedule (tile is then the gather tile it stands in for); path
+  // TTGT: the lowering an untuned plan chooses (one copied operand)
   int packed = 0;
 };
 
