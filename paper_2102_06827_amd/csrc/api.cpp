@@ -844,6 +844,10 @@ bool fused3_rule(const comet_plan_s *p) {
   if (mnk * double(an.nb) >= kFused3Max) return false;
   const double slices = 6.0 * (double(an.m) + double(an.n) + 512) * (double(an.k) + 64);
   if (an.nb > 1 || std::min(an.m, an.n) < 64 || slices > COMET_NOALLOC_SCRATCH_BYTES) return true;
+  // (the estimate leaves out the exponents: 65 x 172829 x 65 passes it and
+  // needs 134.24 MB of 134.22)
+  SplitPlan sp;
+  if (!split_prepare(an, sp).ok() || sp.ws_bytes > COMET_NOALLOC_SCRATCH_BYTES) return true;
   const bool vec = p->vecA_tables && p->vecB_tables &&
                    (an.layoutA == LAYOUT_K_CONTIG || an.layoutB == LAYOUT_K_CONTIG);
   return mnk < (vec ? kFused3MaxVec : kFused3MaxElem);
