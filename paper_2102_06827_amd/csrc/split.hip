@@ -538,9 +538,9 @@ __device__ __forceinline__ void split_store(Tout *__restrict__ C, const int64_t 
   auto nl = [&](int j) { return wn0 + j * 16 + (lane & 15); };
   auto inside = [&](int i, int r, int j) { return m0 + ml(i, r) < M && n0 + nl(j) < N; };
   auto value = [&](int i, int j, int r) {
-    const int em = texp[ml(i, r)], en = texp[BM + nl(j)];
-    const double prod = (em == kExpNone || en == kExpNone) ? 0.0 : ldexp(val(i, j, r), em + en);
-    return Te(alpha * prod);
+    // (a row of zeros has exponent kExpNone and only zero slices: the sum is 0,
+    // or NaN where the other operand holds an infinity or a NaN, and stays so)
+    return Te(alpha * ldexp(val(i, j, r), texp[ml(i, r)] + texp[BM + nl(j)]));
   };
   auto put = [&](Tout v, int64_t at) {
     if constexpr (STREAM)

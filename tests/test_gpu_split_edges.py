@@ -26,3 +26,30 @@ def test_slices_at_the_scratch_limit(n, fused):
     C = torch.full((65, n), float("nan"), device="cuda")
     plan.execute_noalloc(Ad, Bd, C)
     assert torch.equal(C.cpu(), A @ B.T)
+
+
+@pytest.mark.parametrize("compute", ["split_bf16x3", "split_fp16x2"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("size", [(407, 409, 407), (130, 200, 100), (2049, 2047, 65)])
+def test_not_finite_times_a_row_of_zeros(size, dtype, compute):
+    """NaN and infinities of one operand reach every output of their column,
+    also those of the other operand's rows of zeros; the other columns stay
+    exact."""
+    m, n, k = size
+    print_case("zero rows", size, str(dtype), compute)
+    g = torch.Generator().manual_seed(99)
+    A = torch.randint(-3, 4, (m, k), generator=g).to(dtype)
+    B = torch.randint(-3, 4, (k, n), generator=g).to(dtype)
+    A[0], A[m // 2], A[m - 1] = 0, 0, 0
+    B[3, 0], B[k - 1, n // 2], B[5, n - 1] = float("nan"), float("inf"), float("-inf")
+    B[:, 7] = 0
+    bad = torch.zeros(n, dtype=torch.bool)
+    bad[[0, n // 2, n - 1]] = True
+    got = comet.contract("ij=ik*kj", A.cuda(), B.cuda(), compute=compute).cpu()
+    zero = [0, m // 2, m - 1]
+    assert torch.isnan(got[zero][:, bad]).all()
+    assert not torch.isfinite(got[:, bad]).any()
+    assert torch.equal(got[:, ~bad], (A @ torch.where(torch.isfinite(B), B, torch.zeros_like(B)))[:, ~bad])
+    # and the other way round
+    got = comet.contract("ij=ki*kj", B.cuda(), A.T.contiguous().cuda(), compute=compute).cpu()
+    assert torch.isnan(got[bad][:, zero]).all() and not torch.isfinite(got[bad]).any()
