@@ -658,7 +658,10 @@ constexpr double kPackedStore[2][2][kPackedTiles] = {
     {{3.60e6, 4.36e6, 3.90e6, 3.55e6, 3.58e6}, {2.45e6, 3.95e6, 3.50e6, 3.15e6, 3.07e6}},
     {{3.50e6, 3.60e6, 3.40e6, 2.75e6, 2.80e6}, {2.75e6, 2.75e6, 2.50e6, 2.25e6, 2.05e6}},
 };
-constexpr int64_t kPackedEntryK = 96;              // see packed_choice
+// batch entries on the vector-load tiles (see packed_choice): summation
+// indices; outputs of an FP64 entry from which its line is another
+constexpr int64_t kVecEntryK = 96, kVecEntryKSmall = 64;
+constexpr int64_t kVecEntryOut = int64_t(1) << 18, kVecEntryOutPart = int64_t(1) << 20;
 constexpr int64_t kPackedHalfK = 16, kPackedHalfOut = int64_t(1) << 24;   // the same
 constexpr int kPackedMinSteps = 2;                 // fewest steps a share should hold
 
@@ -696,23 +699,34 @@ void packed_choice(comet_plan_s *p, int cus, bool gather_forced) {
   an.packed = an.packed_whole = an.packed_shares = 0;
   const char *env = std::getenv("COMET_PACKED");
   if (!p->pk.am || gather_forced || an.shortk > 0 || (env && std::strcmp(env, "0") == 0)) return;
-  // Batch entries of one or two tiles and a short summation, read in vectors,
-  // are bound by their loads: the vector-load tiles move twice the bytes per
-  // instruction (4096 x 64^3 in FP64 65 us against 70, 500 x 96^3 33 against
-  // 36; FP32 36 against 42 and 21 against 23; but 4000 x 32^3, whose entries
-  // half fill their tile, 32 against 23, and 300 x 100^3 34 against 31).
-  const bool vec = p->vecA_tables && p->vecB_tables;
-  if (!an.X.empty() && vec && an.k <= kPackedEntryK && an.m > 32 && an.n > 32) return;
-  const int dt = an.dtype == COMET_F64 ? 0 : 1;
-  // FP32 with half a step of summation, read in vectors, and C in whole
-  // segments (K = 12, 3072 x 2304: 9.7 us against 12.2; K = 15, 3840 x 3600:
-  // 16.0 / 19.3; but K = 16, 4096 x 4096: 26.8 / 21.8)
-  if (dt == 1 && vec && an.X.empty() && an.k <= kPackedHalfK && p->pk.c_segments && an.m * an.n < kPackedHalfOut) return;
-  const size_t limit = COMET_NOALLOC_SCRATCH_BYTES;
-  const size_t budget = p->ws_taken > limit ? SIZE_MAX : limit - p->ws_taken;
   int ft = -1;
   long fw = 0, fs = 0;
   if (env && *env && std::sscanf(env, "%d,%ld,%ld", &ft, &fw, &fs) < 1) ft = -1;
+  const bool forced = ft >= 0;
+  const int dt = an.dtype == COMET_F64 ? 0 : 1;
+  const bool vec = p->vecA_tables && p->vecB_tables;
+  // Batch entries with a short summation, read in vectors and written in
+  // whole segments, are bound by their loads: the vector-load tiles move twice
+  // the bytes per instruction.  us, vector-load tiles / packed: FP32 4096 x
+  // 64^3 38 / 42, 500 x 160^2 x 64 39 / 41, 64 x 512^2 x 32 24 / 28, 16 x
+  // 2048^2 x 64 110 / 123 (but 40 x 1200^2 x 96 157 / 141); FP64, with half as
+  // many loads per product, 1000 x 96^2 x 64 51 / 52, 64 x 512^2 x 64 59 / 62,
+  // but 500 x 160^2 x 96 92 / 80, 300 x 192^2 x 96 61 / 57, and on large
+  // entries 16 x 2048^2 x 96 276 / 285, 40 x 1200^2 x 96 266 / 266.  Partial
+  // segments of C, which those tiles store past the caches: FP32 500 x 100^2
+  // x 32 20 / 14, 64 x 700^2 x 48 96 / 64, 8 x 2800 x 3000 x 64 201 / 129; FP64
+  // 64 x 700^2 x 48 140 / 97, but 32 x 1504 x 1700 x 80 347 / 361.
+  if (!forced && !an.X.empty() && vec && an.m > 32 && an.n > 32 && an.k <= kVecEntryK) {
+    const int64_t out = an.m * an.n;
+    if (p->pk.c_segments ? dt == 1 || an.k <= kVecEntryKSmall || out > kVecEntryOut : dt == 0 && out > kVecEntryOutPart)
+      return;
+  }
+  // FP32 with half a step of summation, read in vectors, and C in whole
+  // segments (K = 12, 3072 x 2304: 9.7 us against 12.2; K = 15, 3840 x 3600:
+  // 16.0 / 19.3; but K = 16, 4096 x 4096: 26.8 / 21.8)
+  if (!forced && dt == 1 && vec && an.X.empty() && an.k <= kPackedHalfK && p->pk.c_segments && an.m * an.n < kPackedHalfOut) return;
+  const size_t limit = COMET_NOALLOC_SCRATCH_BYTES;
+  const size_t budget = p->ws_taken > limit ? SIZE_MAX : limit - p->ws_taken;
   PackedLaunch &k = p->pk;
   double best = 1e300;
   size_t best_ws = 0;
