@@ -736,7 +736,7 @@ void packed_choice(comet_plan_s *p, int cus, bool gather_forced) {
     packed_tile_shape(tile, dt, &bm, &bn, &bk);
     const int64_t tm = (an.m + bm - 1) / bm, tn = (an.n + bn - 1) / bn, T = tm * tn, nk = (an.k + bk - 1) / bk;
     const size_t slot = size_t(bm) * bn * elem_size(an.dtype);
-    const int res = packed_occupancy(tile, dt, an.layoutA, an.layoutB);
+    const int res = packed_occupancy(tile, dt, an.layoutA, an.layoutB, int(an.k));
     if (res <= 0 || T > INT32_MAX / 2 || T * an.nb > (int64_t(1) << 40)) continue;
     const int64_t C = std::max(cus, 1), S = C * res;
     auto consider = [&](int64_t whole, int64_t shares) {

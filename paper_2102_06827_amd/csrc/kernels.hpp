@@ -152,8 +152,8 @@ struct PackedLaunch {
 };
 hipError_t launch_packed(const PackedLaunch &g, hipStream_t s);
 void packed_tile_shape(int tile, int dtype, int *bm, int *bn, int *bk);
-// workgroups of a tile that fit on one CU
-int packed_occupancy(int tile, int dtype, int layoutA, int layoutB);
+// workgroups of a tile that fit on one CU, for a summation of K indices
+int packed_occupancy(int tile, int dtype, int layoutA, int layoutB, int K);
 
 // C[offCb[b] + offCm[m] + offCn[n]] = beta * C over NB batch entries
 // (offCb == nullptr: NB must be 1 and offCb[0] reads as 0); beta == 0 writes

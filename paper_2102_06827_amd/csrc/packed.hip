@@ -94,16 +94,18 @@ constexpr PackedTile packed_tile(int tile) {
 // us; 512^3 4.1e-7 / 1.5e-7, 11.1 / 11.5; 960^3 5.6e-7 / 2.0e-7; 1200^3 6.2e-7
 // / 2.2e-7, 43.9 / 44.3; 1725^3 7.4e-7 / 2.1e-7, 108 / 109; 3072^3 9.5e-7 /
 // 4.0e-7, 440 / 441.  (A fold every step or two on the small tiles: 256^3 7.3
-// to 7.6 us, 512^3 11.6 to 12.2, 1200^3 45.3 to 46.7.)
+// to 7.6 us, 512^3 11.6 to 12.2, 1200^3 45.3 to 46.7.)  Summations of at most
+// kPackedChain indices keep one accumulator: they are no longer than the
+// chains above, and clearing and adding the sets would be felt (4000 entries
+// of 32^3 16.4 us, 19.9 with them; 98304 x 32 x 96 14.8 and 15.4).
 constexpr int kSets32[] = {1, 1, 1, 8, 8}, kFold32[] = {16, 4, 4, 0, 0};
+constexpr int kPackedChain = 128;
 template <typename T>
-constexpr int packed_sets(int tile) { return sizeof(T) == 8 ? 1 : kSets32[tile]; }
-template <typename T>
-constexpr int packed_fold(int tile) { return sizeof(T) == 8 ? 0 : kFold32[tile]; }
-template <typename T, int TILE, int LA, int LB>
+constexpr bool packed_long(int K) { return sizeof(T) == 4 && K > kPackedChain; }
+template <typename T, int TILE, int LA, int LB, bool LONG>
 using PackedKernel = PackedCore<T, packed_tile<T>(TILE).bm, packed_tile<T>(TILE).bn, packed_tile<T>(TILE).bk,
-                                packed_tile<T>(TILE).wgm, packed_tile<T>(TILE).wgn, LA, LB, packed_sets<T>(TILE),
-                                packed_fold<T>(TILE)>;
+                                packed_tile<T>(TILE).wgm, packed_tile<T>(TILE).wgn, LA, LB, LONG ? kSets32[TILE] : 1,
+                                LONG ? kFold32[TILE] : 0>;
 
 // The workspace slot of share s's piece of shared tile t.  Along the steps
 // each piece has a larger s or a larger t than the one before, so s + t
@@ -116,11 +118,12 @@ __device__ __forceinline__ int64_t piece_slot(int s, int t, bool begun_here, int
 // first step of share s of S over I steps
 __device__ __forceinline__ int64_t share_begin(int64_t I, int S, int s) { return I * s / S; }
 
-// STREAM: C is written with nontemporal stores.
-template <typename T, int TILE, int LA, int LB, bool STREAM>
+// STREAM: C is written with nontemporal stores.  LONG: the accumulators of
+// packed_long.
+template <typename T, int TILE, int LA, int LB, bool STREAM, bool LONG>
 __global__ __launch_bounds__(64 * packed_tile<T>(TILE).wgm * packed_tile<T>(TILE).wgn, packed_tile<T>(TILE).wpe) void
 packed_kernel(PackedLaunch g) {
-  typedef PackedKernel<T, TILE, LA, LB> P;
+  typedef PackedKernel<T, TILE, LA, LB, LONG> P;
   typedef typename P::WT WT;
   __shared__ __attribute__((aligned(16))) T smem[P::LDS];
   __shared__ int64_t ctab_s[P::BM + P::BN];
@@ -156,17 +159,19 @@ packed_kernel(PackedLaunch g) {
     group_coords(is_whole ? xcd_remap(b, g.whole) : g.whole + tt, g.tilesM, g.tilesN, &tm, &tn);
     const int m0 = __builtin_amdgcn_readfirstlane(tm * P::BM), n0 = __builtin_amdgcn_readfirstlane(tn * P::BN);
     // (What depends on the thread alone is the same for every piece: the
-    // compiler would work the epilogue's addresses out ahead of the loop, hold
-    // them over the products and, in the FP64 128 x 128 kernels, spill 25 to 32
-    // of them.  A thread index it cannot see through keeps them where they are
-    // used: FP64 3072^3 848 -> 828 us, no scratch.)
+    // compiler works the epilogue's addresses out ahead of the loop, holds
+    // them over the products and, in the FP64 128 x 128 kernels, spills 25 to
+    // 32 of them.  Where registers are short a thread index it cannot see
+    // through keeps them where they are used: FP64 3072^3 848 -> 828 us, no
+    // scratch; elsewhere they are worked out while the loads are awaited, K =
+    // 30, 3000 x 9000, FP64 59.2 us against 60.4.)
     int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
+    if constexpr (TILE == 0 || LONG) asm volatile("" : "+v"(tid));
     WT w;
     typename P::COffsets co;
     co.load(tid, g.c, m0, n0, g.M, g.N);
     P::accumulate(w, ra, rb, g.am + m0, g.ak, g.bk, g.bn + n0, s0, s1, to_lds(smem), co, ctab, tid);
-    asm volatile("" : "+v"(tid));
+    if constexpr (TILE == 0 || LONG) asm volatile("" : "+v"(tid));
     if (s1 - s0 == nk) {
       gett_store_staged<T, T, P::BM, P::BN, P::WGM, P::WGN, false, STREAM>(
           w, C, ctab, ctab + P::BM, g.M, g.N, g.alpha, g.beta, m0, n0, nullptr, tid);
@@ -188,7 +193,7 @@ packed_kernel(PackedLaunch g) {
 template <typename T, int TILE, bool STREAM>
 __global__ __launch_bounds__(64 * packed_tile<T>(TILE).wgm * packed_tile<T>(TILE).wgn) void packed_fixup_kernel(
     PackedLaunch g) {
-  typedef PackedKernel<T, TILE, 0, 0> P;
+  typedef PackedKernel<T, TILE, 0, 0, false> P;
   typedef typename P::WT WT;
   typedef typename WT::acc_t acc_t;
   const int nk = (g.K + P::BK - 1) / P::BK;
@@ -212,9 +217,9 @@ __global__ __launch_bounds__(64 * packed_tile<T>(TILE).wgm * packed_tile<T>(TILE
                                                                   int64_t(tm) * P::BM, int64_t(tn) * P::BN);
 }
 
-template <typename T, int TILE, int LA, int LB, bool STREAM>
+template <typename T, int TILE, int LA, int LB, bool STREAM, bool LONG>
 hipError_t packed_s(const PackedLaunch &g, hipStream_t s) {
-  typedef PackedKernel<T, TILE, LA, LB> P;
+  typedef PackedKernel<T, TILE, LA, LB, LONG> P;
   const int64_t tiles = int64_t((g.M + P::BM - 1) / P::BM) * ((g.N + P::BN - 1) / P::BN);
   const int64_t nk = (g.K + P::BK - 1) / P::BK;
   if (g.tilesM != (g.M + P::BM - 1) / P::BM || g.tilesN != (g.N + P::BN - 1) / P::BN || g.whole < 0 ||
@@ -227,7 +232,7 @@ hipError_t packed_s(const PackedLaunch &g, hipStream_t s) {
     for (int64_t e0 = 0; e0 < g.entries; e0 += kMaxY) {
       PackedLaunch q = g;
       q.first = e0;
-      hipLaunchKernelGGL((packed_kernel<T, TILE, LA, LB, STREAM>),
+      hipLaunchKernelGGL((packed_kernel<T, TILE, LA, LB, STREAM, LONG>),
                          dim3(unsigned(g.whole), unsigned(g.entries - e0 < kMaxY ? g.entries - e0 : kMaxY)),
                          dim3(P::NT), 0, s, q);
       const hipError_t e = hipGetLastError();
@@ -235,7 +240,7 @@ hipError_t packed_s(const PackedLaunch &g, hipStream_t s) {
     }
     return hipSuccess;
   }
-  hipLaunchKernelGGL((packed_kernel<T, TILE, LA, LB, STREAM>), dim3(unsigned(g.whole + g.shares)), dim3(P::NT), 0, s,
+  hipLaunchKernelGGL((packed_kernel<T, TILE, LA, LB, STREAM, LONG>), dim3(unsigned(g.whole + g.shares)), dim3(P::NT), 0, s,
                      g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || g.shares == 0) return e;
@@ -244,18 +249,25 @@ hipError_t packed_s(const PackedLaunch &g, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, int TILE, int LA, int LB>
-hipError_t packed_l(const PackedLaunch &g, int *occupancy, hipStream_t s) {
+template <typename T, int TILE, int LA, int LB, bool LONG>
+hipError_t packed_n(const PackedLaunch &g, int *occupancy, hipStream_t s) {
   if (occupancy)
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(occupancy, packed_kernel<T, TILE, LA, LB, true>,
-                                                        PackedKernel<T, TILE, LA, LB>::NT, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(occupancy, packed_kernel<T, TILE, LA, LB, true, LONG>,
+                                                        PackedKernel<T, TILE, LA, LB, LONG>::NT, 0);
   // C past the caches only where every store writes whole 64-byte segments.
   // Whole segments: streaming is faster (K = 32, FP64, 8192 x 16384 with
   // C in runs of 16: 266 us against 309).  Parts of one: the neighbours'
   // stores have to meet in the cache (K = 31, 6975 x 14415, runs of 15: 530
   // us streamed, 219 us plain; FP32 549 and 154 us).
   const bool stream = g.c_segments && reinterpret_cast<uintptr_t>(g.C) % 64 == 0;
-  return stream ? packed_s<T, TILE, LA, LB, true>(g, s) : packed_s<T, TILE, LA, LB, false>(g, s);
+  return stream ? packed_s<T, TILE, LA, LB, true, LONG>(g, s) : packed_s<T, TILE, LA, LB, false, LONG>(g, s);
+}
+
+template <typename T, int TILE, int LA, int LB>
+hipError_t packed_l(const PackedLaunch &g, int *occupancy, hipStream_t s) {
+  if constexpr (sizeof(T) == 4)
+    if (packed_long<T>(g.K)) return packed_n<T, TILE, LA, LB, true>(g, occupancy, s);
+  return packed_n<T, TILE, LA, LB, false>(g, occupancy, s);
 }
 
 template <typename T, int TILE>
@@ -293,12 +305,12 @@ hipError_t launch_packed(const PackedLaunch &g, hipStream_t s) {
   return g.dtype == 0 ? packed_d<double>(g, nullptr, s) : packed_d<float>(g, nullptr, s);
 }
 
-int packed_occupancy(int tile, int dtype, int layoutA, int layoutB) {
+int packed_occupancy(int tile, int dtype, int layoutA, int layoutB, int K) {
   static std::mutex mu;
-  static std::map<std::array<int, 5>, int> known;   // it depends on the kernel alone
+  static std::map<std::array<int, 6>, int> known;   // it depends on the kernel alone
   int device = 0;
   (void)hipGetDevice(&device);
-  const std::array<int, 5> key = {device, tile, dtype, layoutA, layoutB};
+  const std::array<int, 6> key = {device, tile, dtype, layoutA, layoutB, dtype == 1 && packed_long<float>(K)};
   std::lock_guard<std::mutex> lk(mu);
   const auto it = known.find(key);
   if (it != known.end()) return it->second;
@@ -307,6 +319,7 @@ int packed_occupancy(int tile, int dtype, int layoutA, int layoutB) {
   g.dtype = dtype;
   g.layoutA = layoutA;
   g.layoutB = layoutB;
+  g.K = K;
   int n = 0;
   const hipError_t e = dtype == 0 ? packed_d<double>(g, &n, nullptr) : packed_d<float>(g, &n, nullptr);
   if (e != hipSuccess) {
