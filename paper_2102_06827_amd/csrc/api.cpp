@@ -732,8 +732,8 @@ void packed_choice(comet_plan_s *p, int cus, bool gather_forced) {
   size_t best_ws = 0;
   for (int tile = 0; tile < kPackedTiles; ++tile) {
     if (ft >= 0 && tile != ft) continue;
-    int bm, bn, bk;
-    packed_tile_shape(tile, dt, &bm, &bn, &bk);
+    int bm, bn, bk, threads;
+    packed_tile_shape(tile, dt, &bm, &bn, &bk, &threads);
     const int64_t tm = (an.m + bm - 1) / bm, tn = (an.n + bn - 1) / bn, T = tm * tn, nk = (an.k + bk - 1) / bk;
     const size_t slot = size_t(bm) * bn * elem_size(an.dtype);
     const int res = packed_occupancy(tile, dt, an.layoutA, an.layoutB, int(an.k));
@@ -741,7 +741,7 @@ void packed_choice(comet_plan_s *p, int cus, bool gather_forced) {
     const int64_t C = std::max(cus, 1), S = C * res;
     auto consider = [&](int64_t whole, int64_t shares) {
       const size_t ws = size_t(shares + std::min(shares, T - whole)) * slot;
-      if (ws > budget) return;
+      if (ws > budget || !packed_grid_fits(threads, T, whole, shares)) return;
       const double us = packed_time_us(dt, tile, res, int(C), T * an.nb, nk, slot, whole, shares,
                                     p->pk.c_segments != 0);
       if (us >= best) return;

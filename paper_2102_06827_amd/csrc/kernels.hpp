@@ -151,7 +151,13 @@ struct PackedLaunch {
   int c_segments;             // C's offsets come in whole, aligned 64-byte segments along n
 };
 hipError_t launch_packed(const PackedLaunch &g, hipStream_t s);
-void packed_tile_shape(int tile, int dtype, int *bm, int *bn, int *bk);
+void packed_tile_shape(int tile, int dtype, int *bm, int *bn, int *bk, int *threads);
+// Whether a schedule's launches stay within 2^32 work-items each: the tiles and
+// shares, and the fix-up of the shared tiles.
+inline bool packed_grid_fits(int64_t threads, int64_t tiles, int64_t whole, int64_t shares) {
+  const int64_t limit = int64_t(UINT32_MAX) / threads;
+  return whole + shares <= limit && (shares == 0 || tiles - whole <= limit);
+}
 // workgroups of a tile that fit on one CU, for a summation of K indices
 int packed_occupancy(int tile, int dtype, int layoutA, int layoutB, int K);
 

@@ -225,7 +225,7 @@ hipError_t packed_s(const PackedLaunch &g, hipStream_t s) {
   if (g.tilesM != (g.M + P::BM - 1) / P::BM || g.tilesN != (g.N + P::BN - 1) / P::BN || g.whole < 0 ||
       g.whole > tiles || g.shares < 0 || (g.shares == 0) != (g.whole == tiles) ||
       int64_t(g.shares) > (tiles - g.whole) * nk || int64_t(g.whole) + g.shares > INT32_MAX || (g.shares && !g.ws) ||
-      (int64_t(g.whole) + g.shares) * P::NT > int64_t(UINT32_MAX) || (g.xa && (g.shares || !g.xb || !g.xc)))
+      !packed_grid_fits(P::NT, tiles, g.whole, g.shares) || (g.xa && (g.shares || !g.xb || !g.xc)))
     return hipErrorInvalidValue;
   if (g.xa) {
     constexpr int64_t kMaxY = 65535;   // grid limit along y
@@ -294,11 +294,12 @@ hipError_t packed_d(const PackedLaunch &g, int *occupancy, hipStream_t s) {
 
 }  // namespace
 
-void packed_tile_shape(int tile, int dtype, int *bm, int *bn, int *bk) {
+void packed_tile_shape(int tile, int dtype, int *bm, int *bn, int *bk, int *threads) {
   const PackedTile &p = dtype == 0 ? kPacked64[tile] : kPacked32[tile];
   *bm = p.bm;
   *bn = p.bn;
   *bk = p.bk;
+  *threads = 64 * p.wgm * p.wgn;
 }
 
 hipError_t launch_packed(const PackedLaunch &g, hipStream_t s) {
