@@ -235,7 +235,11 @@ comet_status_t comet_plan_destroy(comet_plan_t plan);
  * one GPU share that GPU's buffer, which keeps whatever the last call left
  * (every plan writes each workspace byte before reading it, so nothing needs
  * clearing): calls that may overlap in time on one GPU (two streams, or two
- * threads) race on it and must be ordered by the caller.  The first call on a
+ * threads) race on it and must be ordered by the caller.  A plan whose
+ * comet_plan_workspace_size is 0 leaves the buffer alone, but which plans those
+ * are is the planner's choice and may change with a version: FP32
+ * SPLIT_BF16X3 plans of 2^26 multiply-adds and more, for one, and plans that
+ * copy one operand need it.  The first call on a
  * device looks up that device's buffer address (hipGetSymbolAddress), which
  * is not capturable; later calls are.
  */

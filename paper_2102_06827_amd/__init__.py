@@ -173,6 +173,14 @@ def _stream_handle(stream):
     return stream.cuda_stream
 
 
+def _capturing(stream):
+    """Whether the stream (None: the current one) is being captured."""
+    if stream is None:
+        return torch.cuda.is_current_stream_capturing()
+    with torch.cuda.stream(stream):
+        return torch.cuda.is_current_stream_capturing()
+
+
 def _dtype_code(*ts):
     dt = ts[0].dtype
     for t in ts:
@@ -358,6 +366,8 @@ def autotune(cache_path=None, mode=1):
 class Plan:
     """A planned contraction for fixed shapes/strides (capturable execute)."""
 
+    KEEP_WORKSPACES = 4   # streams' workspaces that a plan keeps
+
     def __init__(self, spec, A_like, B_like, C_like=None, compute="default", path="auto"):
         ext, cshape = extents_of(spec, A_like.shape, B_like.shape)
         self.spec = spec
@@ -371,7 +381,8 @@ class Plan:
         n = ctypes.c_size_t()
         _check(lib().comet_plan_workspace_size(self._h, ctypes.byref(n)))
         self.workspace_bytes = n.value
-        self._ws = {}
+        self._ws = {}               # by device and stream, the oldest first
+        self._ws_captured = set()   # those a graph may hold
 
     def describe(self):
         buf = ctypes.create_string_buffer(1 << 16)
@@ -380,14 +391,25 @@ class Plan:
 
     def workspace(self, device, stream=None):
         """The plan's workspace for a stream (one each: executions on two
-        streams may overlap), None if it needs none."""
+        streams may overlap), None if it needs none.  A plan keeps those of
+        KEEP_WORKSPACES streams, a further stream's replaces the oldest; one
+        that a graph capture was given stays until the plan goes (one made
+        during the capture lies in the graph's memory pool: pass a workspace
+        of your own where that is not wanted)."""
         if not self.workspace_bytes:
             return None
         key = (device, _stream_handle(stream))
         ws = self._ws.get(key)
+        if ws is not None and (key in self._ws_captured or not _capturing(stream)):
+            return ws
+        if _capturing(stream):
+            self._ws_captured.add(key)
         if ws is None:
             with torch.cuda.stream(stream):   # freed in this stream's order (None: the current one)
                 ws = self._ws[key] = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=device)
+            loose = [k for k in list(self._ws) if k not in self._ws_captured]
+            if len(loose) > self.KEEP_WORKSPACES:
+                self._ws.pop(loose[0], None)
         return ws
 
     def __call__(self, A, B, C=None, alpha=1.0, beta=0.0, workspace=None, stream=None):
