@@ -125,8 +125,11 @@ int batch_blocks_per_cu(int dtype, int mode);
 
 // The packed gather kernel (packed.hip): FP64 or FP32 storage and arithmetic,
 // any strides, operands of less than kPackedMaxBytes.  am, ak, bk, bn are the
-// offset tables in bytes, the row tables padded to a multiple of kPackedRowPad
-// and the summation tables by kPackedKPad entries, with their last entry.
+// offset tables in bytes: the row tables padded to a multiple of kPackedRowPad
+// with their last entry, the summation tables by kPackedKPad entries of
+// kPackedOut.  That one lies past every operand, whatever is added to it, so
+// that loads of indices past the summation's end give zeros; nothing else
+// masks the last, partial step.
 // Tiles 0 .. whole - 1 (in the XCD-aware order) are computed by a workgroup
 // each; `shares` workgroups split the steps of the others, whose partial
 // tiles take (shares + min(shares, others)) * bm * bn elements of ws.

@@ -9,14 +9,16 @@
 //
 //   * Offsets are 32-bit byte offsets (operands below 2 GiB).  An operand
 //     contiguous along its rows has one row offset per thread, in a vector
-//     register, and its summation offsets in scalar registers: a buffer load
-//     adds the two, so an element costs one instruction.  An operand
-//     contiguous along the summation has the summation offset in a vector
-//     register, one per step, and one vector addition per element.
+//     register, and its summation offsets in scalar registers; one contiguous
+//     along the summation has the summation offset in a vector register, one
+//     per step.  Either way an element costs one 32-bit addition and one
+//     buffer load: the sum is the load's vector offset, which its bounds check
+//     sees whole.
 //   * 64 lanes read 64 consecutive elements (or 64 / BK runs of BK), so the
 //     loads are as coalesced as the operand allows.  Rows past the edge read
 //     the last row (the tables are padded with it), whose products are never
-//     stored; only the last, partial summation step masks anything.
+//     stored; indices past the summation's end have offsets out of the
+//     operand's bounds and load zeros.  Nothing is masked.
 //   * Every LDS tile is stored [row][k] with a 16-byte pad, whatever the
 //     operand's order: a thread that walks the summation writes its 16 bytes
 //     of consecutive k at once.  A lane then reads 16 bytes of one row for 2

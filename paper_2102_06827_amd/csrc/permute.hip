@@ -455,8 +455,7 @@ hipError_t launch_perm_t(const PermuteLaunch &p, hipStream_t s) {
   if (std::min(sh.EI, sh.EO) <= TS) {
     const TileArgs a = tile_args(sh, TS);
     const int64_t tiles = tile_blocks(sh, a), groups = (tiles + 3) / 4;
-    const int64_t whole = tile_blocks(sh, tile_args(sh, TP));
-    if (tiles < 4 * whole && groups < (int64_t(1) << 24)) {
+    if (groups < (int64_t(1) << 24)) {
       if (small)
         hipLaunchKernelGGL((permute_small<T, uint32_t>), dim3(unsigned(groups)), dim3(256), 0, s, in, out, a, tiles,
                            p.alpha, p.beta);

@@ -37,8 +37,8 @@ def test_grid_rule(tmp_path):
         (256, lim, lim - 5, 5): 1, (256, lim, lim - 5, 6): 0,
         # all tiles shared: the fix-up has a workgroup for each of them
         (256, lim, 0, 512): 1, (256, lim + 1, 0, 512): 0,
-        # 65 x 2^29 outputs on 32 x 64 tiles, and on 128 x 128 of 256 threads
-        (256, 3 * 2**23, 3 * 2**23, 0): 0, (256, 2**22, 2**22, 0): 1,
+        # 129 x 2^28 outputs on 32 x 64 tiles, and on 128 x 128 of 256 threads
+        (256, 5 * 2**22, 5 * 2**22, 0): 0, (256, 2**22, 2**22, 0): 1,
     }
     r = subprocess.run([exe], input="\n".join("%d %d %d %d" % c for c in cases), capture_output=True, text=True)
     assert [int(x) for x in r.stdout.split()] == list(cases.values())
