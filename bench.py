@@ -61,17 +61,18 @@ HBM_PEAK_GBS = 8000.0
 # counters scaled by a plain 1 GiB copy (profiles/gett_f64_ccsd_v96_o32_hbm_counters.md);
 # valid only for the schedule and kernel version recorded, null otherwise.
 HEADLINE_TRAFFIC = {"schedule": {"path": "gett", "packed": 1, "packed_whole": 512, "packed_shares": 256},
-                    "kernel_version": "k12", "bytes": 1112691917}
-KERNEL_VERSION = "k12"
+                    "kernel_version": "k13", "bytes": 1161106498}
+KERNEL_VERSION = "k13"
 
 
 def headline_kernels(d):
     # the headline's output is whole 128 x 128 tiles over whole K steps: tile
     # 3 runs its unmasked variant (last template argument true)
     if d.get("packed"):
-        # the packed gather kernel: C is written in whole 64-byte segments, so streamed
+        # the packed gather kernel: C is written in whole 64-byte segments, so
+        # streamed; one set of accumulators
         p = d["packed"] - 1
-        return ["packed_kernel<double, %d, 0, 1, true>" % p] + (
+        return ["packed_kernel<double, %d, 0, 1, true, false>" % p] + (
             ["packed_fixup_kernel<double, %d, true>" % p] if d["packed_shares"] else [])
     t = d["tile"]
     full = ", true" if t == 3 else ""
