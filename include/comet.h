@@ -288,8 +288,8 @@ comet_status_t comet_analyze(const char *spec, const int64_t *extents,
  * a batch of copies of a representative problem and caches the winner, and
  * otherwise a throughput model picks the class.  The work list is cut into
  * one queue per XCD; whole problems go to queues by longest processing time
- * first, heaviest first within a queue, each problem's tiles in groups of
- * tile rows.  Workgroups take (problem, tile) items from their XCD's queue
+ * first, within a queue the heaviest first or, where the last items to finish
+ * decide, the longest items first, each problem's tiles in groups of tile rows.  Workgroups take (problem, tile) items from their XCD's queue
  * through a device counter and move on to the other queues once it is
  * drained, so many small, uneven problems fill the GPU together.  A problem
  * whose operands have their unit strides on different summation labels gets
@@ -307,6 +307,8 @@ comet_status_t comet_analyze(const char *spec, const int64_t *extents,
  * contents on entry do not matter.
  * comet_batch_create plans every problem and uploads the work list and
  * offset tables (not capturable); comet_batch_execute is capturable.
+ * Executions of one batch write the same outputs and share its operand
+ * copies: they must not overlap, whatever their workspaces.
  * comet_batch_describe writes JSON: output tiles, persistent grid, mode,
  * problems per tile class, items per queue, how many classes came from the
  * autotuner and how many operand copies run before the launch.
