@@ -87,20 +87,23 @@ constexpr PackedTile packed_tile(int tile) {
 }
 
 // FP32 accumulators of a tile (see PackedCore): eight sets on the tiles of
-// small and mid-size products, a fold every 128 summation indices on 64 x 64
-// and 128 x 64 and every 512 on 128 x 128.  A whole tile would carry all of K
-// in one accumulator, and its error grows by the root of that chain; a
+// small and mid-size products, a fold every 256 summation indices on 64 x 64
+// and 128 x 64 and every 1024 on 128 x 128.  A whole tile would carry all of
+// K in one accumulator, and its error grows by the root of that chain; a
 // schedule that fills the chip with whole tiles is not to cost the accuracy
 // that splitting the summation over workgroups had.  Relative error (uniform
-// operands) and time, one accumulator / so: 256^3 2.9e-7 / 1.1e-7, 7.1 / 7.4
-// us; 512^3 4.1e-7 / 1.5e-7, 11.1 / 11.5; 960^3 5.6e-7 / 2.0e-7; 1200^3 6.2e-7
-// / 2.2e-7, 43.9 / 44.3; 1725^3 7.4e-7 / 2.1e-7, 108 / 109; 3072^3 9.5e-7 /
-// 4.0e-7, 440 / 441.  (A fold every step or two on the small tiles: 256^3 7.3
-// to 7.6 us, 512^3 11.6 to 12.2, 1200^3 45.3 to 46.7.)  Summations of at most
-// kPackedChain indices keep one accumulator: they are no longer than the
-// chains above, and clearing and adding the sets would be felt (4000 entries
-// of 32^3 16.4 us, 19.9 with them; 98304 x 32 x 96 14.8 and 15.4).
-constexpr int kSets32[] = {1, 1, 1, 8, 8}, kFold32[] = {16, 4, 4, 0, 0};
+// operands), split over workgroups / one accumulator / so: 256^3 1.5e-7,
+// 2.9e-7, 1.1e-7; 512^3 1.5e-7, 4.1e-7, 1.5e-7; 960^3 2.1e-7, 5.6e-7, 2.0e-7;
+// 1500^3 4.0e-7, 6.6e-7, 2.8e-7; 3072 x 600 x 1000 3.0e-7, 5.7e-7, 2.9e-7;
+// 3072^3 8.4e-7, 9.5e-7, 5.7e-7.  us, one accumulator / so: 256^3 7.1 / 7.4,
+// 512^3 11.1 / 11.5, 1200^3 44.3 / 44.7, 1725^3 108 / 109, 3072^3 430 / 434.
+// (A fold every step or two on the small tiles: 512^3 11.6 to 12.2, 1200^3 45.3
+// to 46.7; every 128 and 512 indices on the larger ones: 1900^3 144 / 146.)
+// Summations of at most kPackedChain indices keep one accumulator: they are no
+// longer than the chains of the small tiles, and clearing and adding the sets
+// would be felt (4000 entries of 32^3 16.4 us, 19.9 with them; 98304 x 32 x 96
+// 14.8 and 15.4).
+constexpr int kSets32[] = {1, 1, 1, 8, 8}, kFold32[] = {32, 8, 8, 0, 0};
 constexpr int kPackedChain = 128;
 template <typename T>
 constexpr bool packed_long(int K) { return sizeof(T) == 4 && K > kPackedChain; }

@@ -31,7 +31,8 @@ def emulated_error(A, B, L):
 # shared every tile (1024 where only a part of the tiles was shared)
 @pytest.mark.parametrize("spec", ["ij=ik*kj", "ij=ki*jk"])
 @pytest.mark.parametrize("m,n,k,L", [(256, 256, 256, 128), (512, 512, 512, 128), (960, 960, 960, 128),
-                                     (3072, 300, 1000, 128), (1200, 1200, 1200, 192), (1601, 1603, 1599, 1024),
+                                     (3072, 300, 1000, 128), (1200, 1200, 1200, 192),
+                                     (1400, 1400, 1400, 320), (3072, 600, 1000, 320), (1601, 1603, 1599, 1024),
                                      (3072, 3072, 3072, 1024)])
 def test_fp32_error(m, n, k, L, spec):
     print_case("fp32 error", spec, m, n, k)
